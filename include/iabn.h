@@ -39,10 +39,15 @@
  *    in-place pairs.
  *  - Tensor pointers need only the alignment of their element type.  Each
  *    call reads and writes 16-byte accesses where HW and the pointers'
- *    alignment allow, else 8-, 4- or 2-byte ones (a narrower access changes
- *    the order of the sums, not the result beyond rounding).
+ *    alignment allow, else 8-, 4- or 2-byte ones, or 16-byte ones at the
+ *    alignment of an element (another width changes the order of the sums,
+ *    not the result beyond rounding).
  *  - Results are deterministic: the same inputs on the same device give
  *    bit-identical outputs (all reductions combine in a fixed order).
+ *  - The workspace's content before a call does not matter (but see the
+ *    phases below).  Blocks of the slice-resident kernels exchange sums
+ *    through it; no block waits without bound, so calls on different streams
+ *    cannot hold each other up for good.
  *  - The library keeps no device state between calls (except the scratch
  *    of iabn_forward_train_noalloc): calls on different streams may run
  *    concurrently when they share no output or workspace.
@@ -103,10 +108,16 @@ typedef enum {
 /* How an entry point runs a shape. */
 typedef struct {
     int channel_resident; /* 1: one kernel, one block per channel holding the
-                             channel on chip; 0: the streaming kernels (two
-                             passes for the training entry points) */
+                             channel on chip; 0: each channel is cut into
+                             blocks / C slices, by the slice-resident kernels
+                             (training entry points: one kernel, one block per
+                             slice holding it on chip) or the streaming
+                             kernels (two passes for the training entry
+                             points) */
     int access_bytes;     /* bytes per vector access: 16, 8, 4, 2, or the
-                             element size */
+                             element size (rows of the slice-resident kernels
+                             that 16-byte accesses do not divide end in single
+                             elements) */
     int threads;          /* threads per block */
     int reg_accesses;     /* channel-resident: accesses per thread held in
                              registers (per tensor) */

@@ -3,7 +3,9 @@
 Each translation unit of ``csrc/`` compiles to an object file in parallel,
 then one link makes the shared library.  ``build_probe`` compiles the
 benchmark's bandwidth probes (``bench_probe.hip``) into a library of their
-own, ``libiabn_probe.so``; libiabn does not contain or use them.
+own, ``libiabn_probe.so``; libiabn does not contain or use them.  The tests'
+``libiabn_abandon.so`` is libiabn with the fp16 slice-resident kernels built
+to wait for a single poll, so that their abandoned slices can be tested.
 """
 
 from __future__ import annotations
@@ -20,6 +22,9 @@ CSRC = os.path.join(HERE, "csrc")
 SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [os.path.join(ROOT, "include", "iabn.h")]
 LIB = os.path.join(HERE, "libiabn.so")
+ABANDON_LIB = os.path.join(HERE, "libiabn_abandon.so")
+ABANDON_SOURCES = ("slice_fwd_f16.hip", "slice_bwd_f16.hip")
+ABANDON_FLAG = "-DIABN_SLICE_POLLS=1"
 PROBE_SRC = os.path.join(HERE, "bench_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libiabn_probe.so")
 ARCH = "gfx950"
@@ -45,12 +50,19 @@ def build(verbose: bool = False) -> str:
     """Always recompiles; writes libiabn.so next to this file atomically."""
     cc = hipcc()
     with tempfile.TemporaryDirectory(prefix="iabn_build_") as tmp:
-        objs, procs = [], []
-        for src in SOURCES:
-            obj = os.path.join(tmp, os.path.basename(src) + ".o")
-            cmd = [cc] + FLAGS + ["-c", "-o", obj, src]
-            objs.append(obj)
+        objs, abandon, procs = [], [], []
+
+        def compile_(src, obj, extra=()):
+            cmd = [cc] + FLAGS + list(extra) + ["-c", "-o", obj, src]
             procs.append((cmd, _run(cmd)))
+            return obj
+
+        # The largest units first.
+        for src in sorted(SOURCES, key=lambda s: "slice" not in s):
+            name = os.path.basename(src)
+            objs.append(compile_(src, os.path.join(tmp, name + ".o")))
+            abandon.append(compile_(src, os.path.join(tmp, name + ".abandon.o"), [ABANDON_FLAG])
+                           if name in ABANDON_SOURCES else objs[-1])
         errors = []
         for cmd, p in procs:
             out, err = p.communicate()
@@ -60,12 +72,14 @@ def build(verbose: bool = False) -> str:
                 print(err)
         if errors:
             raise RuntimeError("hipcc failed:\n" + "\n".join(errors))
-        out = LIB + ".tmp%d" % os.getpid()
-        cmd = [cc, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", out] + objs
-        res = subprocess.run(cmd, capture_output=True, text=True)
-        if res.returncode != 0:
-            raise RuntimeError("link failed (%d):\n%s\n%s" % (res.returncode, " ".join(cmd), res.stderr))
-        os.replace(out, LIB)
+        for lib, parts in ((LIB, objs), (ABANDON_LIB, abandon)):
+            out = lib + ".tmp%d" % os.getpid()
+            cmd = [cc, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", out] + parts
+            res = subprocess.run(cmd, capture_output=True, text=True)
+            if res.returncode != 0:
+                raise RuntimeError("link failed (%d):\n%s\n%s"
+                                   % (res.returncode, " ".join(cmd), res.stderr))
+            os.replace(out, lib)
     return LIB
 
 

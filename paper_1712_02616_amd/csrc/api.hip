@@ -6,10 +6,13 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
 #include <cmath>
 #include <mutex>
+#include <random>
 
 #include "launch.h"
+#include "tile.h"
 
 #define IABN_VERSION 10100
 
@@ -99,6 +102,168 @@ size_t workspace_bytes_for(int64_t N, int64_t C, int64_t HW) {
     return static_cast<size_t>(C) * static_cast<size_t>(sp.P) * kWaves * sizeof(Partial);
 }
 
+// ---------------------------------------------------------------- slice plan
+
+struct SlicePlan {
+    TileGeom g;
+    int vec;  // elements per access
+    int R;    // accesses per thread the kernel holds
+};
+
+// The tiles of a layer for accesses of `vec` elements (tile.h) by groups of
+// `lanes` threads.  False where a tile does not fit 32-bit byte offsets.
+bool make_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, int lanes, TileGeom* g) {
+    const int64_t ab = static_cast<int64_t>(vec) * eb, row = HW * eb, nstride = C * row;
+    const int64_t vrow = HW / vec, tail = HW % vec, limit = int64_t(1) << 30;
+    if (vrow < 1 || row >= limit) return false;
+    g->C = static_cast<uint32_t>(C);
+    g->lanes = static_cast<uint32_t>(lanes);
+    g->split_rows = vrow > lanes ? 1u : 0u;
+    const int64_t per = g->split_rows ? (vrow + lanes - 1) / lanes : lanes / vrow;
+    if (!g->split_rows && (per + 1) * nstride >= limit) return false;
+    g->tiles = static_cast<uint32_t>(g->split_rows ? N * per : (N + per - 1) / per);
+    g->per = static_cast<uint32_t>(per);
+    g->per_div = iabn_divmagic_make(g->per);
+    g->vrow = static_cast<uint32_t>(vrow);
+    g->vrow_div = iabn_divmagic_make(g->vrow);
+    const int64_t rows = g->split_rows ? 1 : per;  // of a tile
+    const int64_t rows_end = g->split_rows || N % per == 0 ? rows : N % per;
+    g->cap = static_cast<uint32_t>((rows - 1) * nstride + (vrow - 1) * ab);
+    g->cap_end = static_cast<uint32_t>((rows_end - 1) * nstride + (vrow - 1) * ab);
+    g->tile_bytes = static_cast<uint32_t>(lanes * ab);
+    g->wrap_at = g->split_rows ? static_cast<uint32_t>(per * lanes * ab) : UINT32_MAX;
+    g->row_bytes = static_cast<uint64_t>(row);
+    g->nstride = static_cast<uint64_t>(nstride);
+    g->tail = static_cast<uint32_t>(tail);
+    g->tail_div = iabn_divmagic_make(tail ? g->tail : 1u);
+    g->tails = static_cast<uint32_t>(N * tail);
+    g->tail_at = static_cast<uint32_t>(vrow * ab);
+    g->xcd_order = row % kLineBytes != 0 ? 1u : 0u;
+    g->m = static_cast<double>(N) * static_cast<double>(HW);
+    g->inv_m = 1.0 / g->m;
+    return true;
+}
+
+// Cuts the channels into P slices.
+void set_slices(TileGeom* g, int64_t P) {
+    g->P = static_cast<uint32_t>(P);
+    g->step = g->P * (kThreads / g->lanes);
+    if (g->split_rows) {
+        g->step_at = g->step % g->per * g->tile_bytes;
+        g->step_base = g->step / g->per * g->nstride;
+    } else {
+        g->step_at = 0;
+        g->step_base = static_cast<uint64_t>(g->step) * g->per * g->nstride;
+    }
+}
+
+// Rows of at least a cache line that only 2- or 4-byte accesses divide (or
+// tensors aligned to no more) move in 16-byte accesses at element alignment
+// (ragged rows, tile.h).
+constexpr int64_t kRaggedMinRowBytes = kLineBytes;
+// Channels of more values than this take the slice-resident kernels where
+// rows are ragged; smaller ones fit the channel-resident kernels' narrow
+// accesses, whose code is shorter: (8, 512, 21x21) fp16 (3528 values) 6.4 /
+// 7.9 us against 5.6 / 6.3, (8, 1024, 27x27) (5832) 10.4 / 13.9 against 12.0
+// / 15.0, (8, 1024, 65x65) 38.9 / 53.7 against 55.3 / 70.9, (8, 256, 129x129)
+// 35.5 / 51.0 against 115 / 143.
+constexpr int64_t kRaggedMinChannel = 4096;
+
+bool ragged_rows(int64_t HW, int eb, int vec) {
+    return vec * eb <= 4 && HW * eb >= kRaggedMinRowBytes;
+}
+
+// Blocks of the slice-resident kernels that the chip holds at once: two per
+// CU (their registers and LDS, slice_bwd.hip).
+constexpr int64_t kSliceBlocks = 2 * kCUs;
+static_assert(kSliceWords * sizeof(uint64_t) <= kWaves * sizeof(Partial),
+              "a slice's words fit where the streaming kernels keep its partials");
+
+// Where the slice-resident kernels are the better choice (J: 16-byte accesses
+// per thread of a slice, or narrower ones; fp16 unless noted, forward /
+// backward us, against the streaming kernels' two launches, both in a graph).
+// One slice per channel while a thread has at most kOneSliceMaxJ accesses:
+// one launch and no exchange, (2, 16, 8x8) fp32 3.7 / 3.6 against 4.9 / 4.5,
+// (4, 48, 40x40) fp32 J = 5 6.5 / 7.1 against 7.1 / 7.3; J = 8 (2, 16, 64x64)
+// fp32 6.5 / 7.5 against 5.7 / 6.5.  (Few small channels of narrow accesses
+// stay on the streaming kernels, where the training entry points give the
+// same bits as their two phases.)  More slices, as many as the chip holds,
+// from kSlicesMinJ accesses on, where the second read saved is worth the
+// exchange: (32, 64, 56x56) backward J = 6 14.5 against 15.6, (8, 20,
+// 224x224) J = 8 13.3 / 15.6 against 16.9 / 21.6; but (16, 32, 56x56) J = 1.5
+// 8.6 / 9.1 against 7.7 / 8.6.  The exchange of many slices takes longer
+// (more than kFewSlices: (1, 8, 512x512) fp32 J = 4 12.2 / 12.2 against 10.0
+// / 12.0, (2, 8, 1024x1024) J = 16 22.0 / 28.8 against 22.0 / 30.6).  There is
+// no upper bound for 16-byte accesses ((64, 64, 224x224) fp32, J = 392: 395 /
+// 652 against 421 / 697); narrower ones are held 16 deep and gain up to about
+// twice that ((16, 32, 110x110) 13.5 / 15.3 against 14.1 / 16.7, (64, 64,
+// 110x110) J = 47 77.8 / 108 against 58.2 / 86.3).
+constexpr int64_t kOneSliceMaxJ = 6;
+constexpr int64_t kSlicesMinJ = 5;
+constexpr int64_t kFewSlices = 32;
+constexpr int64_t kManySlicesMinJ = 16;
+constexpr int64_t kSliceNarrowMaxJ = 32;
+
+// The slice-resident kernels for a layer whose aligned accesses are `vec`
+// elements wide, or false where the streaming kernels are the better choice.
+// Ragged rows take them whatever their size (the channel-resident and the
+// streaming kernels would move them in 2- or 4-byte accesses).
+bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward, SlicePlan* out) {
+    const bool ragged = ragged_rows(HW, eb, vec);
+    const int v = ragged ? 16 / eb : vec;
+    const bool wide = v * eb == 16;
+    TileGeom a, b;
+    const bool ok64 = make_tiles(N, C, HW, eb, v, 64, &a);
+    const bool ok256 = make_tiles(N, C, HW, eb, v, kThreads, &b);
+    if (!ok64 && !ok256) return false;
+    const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
+    const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
+    out->g = slots64 < slots256 ? a : b;
+    out->vec = v;
+    TileGeom& g = out->g;
+    const Split sp = split_channel(N * HW, C);
+    const int64_t groups = kThreads / g.lanes;
+    auto accesses = [&](int64_t P) { return (int64_t(g.tiles) + P * groups - 1) / (P * groups); };
+    int64_t P = kSliceBlocks / C;
+    if (P > sp.P) P = sp.P;
+    if (P > kMaxSlicesOnChip) P = kMaxSlicesOnChip;
+    if (P < 1 || accesses(1) <= kOneSliceMaxJ) P = 1;
+    const int64_t J = accesses(P);
+    set_slices(&g, P);
+    const int* rungs = !wide ? kSliceNarrowRungs : backward ? kSliceBwdRungs : kSliceFwdRungs;
+    const int n = !wide      ? int(sizeof kSliceNarrowRungs / sizeof(int))
+                  : backward ? int(sizeof kSliceBwdRungs / sizeof(int))
+                             : int(sizeof kSliceFwdRungs / sizeof(int));
+    out->R = rungs[n - 1];
+    for (int i = n - 1; i >= 0; --i)
+        if (J <= rungs[i]) out->R = rungs[i];
+    if (ragged && N * HW > kRaggedMinChannel) return true;
+    if (!wide && J > kSliceNarrowMaxJ) return false;
+    if (P > 1) return J >= (P <= kFewSlices ? kSlicesMinJ : kManySlicesMinJ);
+    return C >= kFusedMinChannels || (vec * eb == 16 && J <= kOneSliceMaxJ);
+}
+
+// Workspace bytes a slice-resident launch uses.
+size_t slice_workspace(const SlicePlan& p) {
+    return p.g.P > 1 ? static_cast<size_t>(p.g.C) * p.g.P * kSliceWords * sizeof(uint64_t) : 0;
+}
+
+// The tag and the key of one launch (tile.h): a count that is never 0 and not
+// repeated for 2^48 launches, starting at a random place so that what an
+// earlier process left in memory holds no tag of this one, and 64 bits that
+// differ in both halves from launch to launch (2^64 over the golden ratio).
+SliceArgs slice_args(void* workspace) {
+    static std::atomic<uint64_t> next{[] {
+        std::random_device rd;
+        return (static_cast<uint64_t>(rd()) << 32) ^ rd();
+    }()};
+    constexpr uint64_t mask = (uint64_t(1) << kTagBits) - 1;
+    uint64_t n;
+    do n = next.fetch_add(1, std::memory_order_relaxed);
+    while ((n & mask) == 0);
+    return {static_cast<uint64_t*>(workspace), n & mask, n * 0x9e3779b97f4a7c15ULL};
+}
+
 // The access geometry for `vec` elements per access.
 Geom make_geom(int64_t N, int64_t C, int64_t HW, int dtype, int vec,
                int64_t target_blocks = kTargetBlocks) {
@@ -170,6 +335,20 @@ int validate_common(int dtype, int64_t N, int64_t C, int64_t HW, bool train) {
 
 bool empty(int64_t N, int64_t C, int64_t HW) { return C == 0 || N * HW == 0; }
 
+// Which kernels a training pass takes: the channel-resident ones, the
+// slice-resident ones, or the streaming ones.
+enum class Route { kChannel, kSlice, kStream };
+
+Route plan_route(int64_t N, int64_t C, int64_t HW, int dtype, const Geom& g, bool backward,
+                 bool narrow_ok, FusedPlan* fp, SlicePlan* sl) {
+    const int eb = elem_bytes(dtype), vec = static_cast<int>(g.vec);
+    if (ragged_rows(HW, eb, vec) && N * HW > kRaggedMinChannel &&
+        plan_slice(N, C, HW, eb, vec, backward, sl))
+        return Route::kSlice;
+    if (plan_fused(C, g, eb, backward, narrow_ok, fp)) return Route::kChannel;
+    return plan_slice(N, C, HW, eb, vec, backward, sl) ? Route::kSlice : Route::kStream;
+}
+
 const char* fwd_name(int fm) {
     return fm == kFwdOut ? "standard forward" : fm == kFwdCkpt ? "checkpointing forward" : "forward";
 }
@@ -201,11 +380,19 @@ int forward_train_impl(int fm, void* x, void* out, int dtype, const float* gamma
                            fm == kFwdInPlace ? nullptr : out, eps, momentum, slope};
     const hipStream_t st = static_cast<hipStream_t>(stream);
     FusedPlan fp;
-    const bool fused = plan_fused(C, g, elem_bytes(dtype), false, fm == kFwdInPlace, &fp);
-    if ((!fused || !ws_if_streaming) &&
+    SlicePlan sl;
+    const Route route = plan_route(N, C, HW, dtype, g, false, fm == kFwdInPlace, &fp, &sl);
+    const bool needs_ws =
+        route == Route::kStream || (route == Route::kSlice && slice_workspace(sl) > 0);
+    if ((needs_ws || !ws_if_streaming) &&
         (rc = check_workspace(N, C, HW, workspace, workspace_bytes)))
         return rc;
-    if (fused) {
+    if (route == Route::kSlice) {
+        if (!launch_fwd_slice(dtype, sl.vec, fm, x, sl.g, sl.R, slice_args(workspace), prm, st))
+            return fail(IABN_ERR_HIP, "no sliced %s kernel built for R=%d", fwd_name(fm), sl.R);
+        return launched(fwd_name(fm));
+    }
+    if (route == Route::kChannel) {
         if (!launch_fwd_fused(dtype, fm, x, g, fp, prm, st))
             return fail(IABN_ERR_HIP, "no %s kernel built for T=%d R=%d", fwd_name(fm), fp.T, fp.R);
         return launched(fwd_name(fm));
@@ -244,7 +431,15 @@ int backward_impl(int bm, bool ii, const void* u, const void* zs, void* dz_dx, i
     const BwdParams prm = {gamma, beta, save_mean, save_var, dgamma, dbeta, eps, slope, ii ? 1 : 0};
     const hipStream_t st = static_cast<hipStream_t>(stream);
     FusedPlan fp;
-    if (plan_fused(C, g, elem_bytes(dtype), true, bm == kBwdFromZ, &fp)) {
+    SlicePlan sl;
+    const Route route = plan_route(N, C, HW, dtype, g, true, bm == kBwdFromZ, &fp, &sl);
+    if (route == Route::kSlice) {
+        if (!launch_bwd_slice(dtype, sl.vec, bm, u, zs, dz_dx, sl.g, sl.R,
+                              slice_args(workspace), prm, st))
+            return fail(IABN_ERR_HIP, "no sliced %s kernel built for R=%d", bwd_name(bm, ii), sl.R);
+        return launched(bwd_name(bm, ii));
+    }
+    if (route == Route::kChannel) {
         if (!launch_bwd_fused(dtype, bm, u, zs, dz_dx, g, fp, prm, st))
             return fail(IABN_ERR_HIP, "no %s kernel built for T=%d R=%d", bwd_name(bm, ii), fp.T, fp.R);
         return launched(bwd_name(bm, ii));
@@ -346,7 +541,10 @@ int iabn_plan(int op, int dtype, int64_t N, int64_t C, int64_t HW, iabn_plan_t* 
     plan->access_bytes = vec * eb;
     plan->xcd_order = static_cast<int>(g.xcd_order);
     FusedPlan fp;
-    if (train && plan_fused(C, g, eb, backward, narrow_ok, &fp)) {
+    SlicePlan sl;
+    const Route route =
+        train ? plan_route(N, C, HW, dtype, g, backward, narrow_ok, &fp, &sl) : Route::kStream;
+    if (route == Route::kChannel) {
         const int64_t past = static_cast<int64_t>(g.vchan) - static_cast<int64_t>(fp.T) * fp.R;
         const int64_t past_per_thread = past > 0 ? (past + fp.T - 1) / fp.T : 0;
         const int64_t lds = fused_lds_accesses(fp.T, backward, op == IABN_OP_STD_BACKWARD);
@@ -359,7 +557,8 @@ int iabn_plan(int op, int dtype, int64_t N, int64_t C, int64_t HW, iabn_plan_t* 
         plan->channels_per_block = fp.cpb;
     } else {
         plan->threads = kThreads;
-        plan->blocks = C * static_cast<int64_t>(g.P);
+        plan->blocks = C * static_cast<int64_t>(route == Route::kSlice ? sl.g.P : g.P);
+        if (route == Route::kSlice) plan->access_bytes = sl.vec * eb;
     }
     return ok();
 }
@@ -418,12 +617,15 @@ int iabn_forward_train_noalloc(void* x_z, int dtype, const float* gamma, const f
     int rc = validate_common(dtype, N, C, HW, true);
     if (rc) return rc;
     if (empty(N, C, HW)) return ok();
-    const size_t need = workspace_bytes_for(N, C, HW);
     const int vec = access_vec(HW, dtype, x_z, nullptr, nullptr);
     FusedPlan fp;
-    const bool fused =
-        plan_fused(C, make_geom(N, C, HW, dtype, vec), elem_bytes(dtype), false, true, &fp);
-    if (!fused && need > kScratchBytes)
+    SlicePlan sl;
+    const Route route =
+        plan_route(N, C, HW, dtype, make_geom(N, C, HW, dtype, vec), false, true, &fp, &sl);
+    const size_t need = route == Route::kChannel ? 0
+                        : route == Route::kSlice ? slice_workspace(sl)
+                                                 : workspace_bytes_for(N, C, HW);
+    if (need > kScratchBytes)
         return fail(IABN_ERR_WORKSPACE,
                     "this shape needs %zu bytes of scratch, more than the %zu the library "
                     "holds per device",

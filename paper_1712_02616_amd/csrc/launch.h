@@ -207,6 +207,57 @@ inline bool fused_strips(const Geom& g, const FusedPlan& fp, bool wide) {
            g.vchan / static_cast<uint32_t>(fp.T) >= static_cast<uint32_t>(fp.R);
 }
 
+// ---- slice-resident kernels (slice_fwd.h, slice_bwd.h)
+
+struct TileGeom;   // tile.h
+struct SliceArgs;  // tile.h
+
+// False if no kernel is built for the access width and R (a planning bug).
+template <int DT>
+bool launch_fwd_slice_dt(int vec, int fm, void* xz, const TileGeom& g, int R, const SliceArgs& sa,
+                         const FwdParams& prm, hipStream_t st);
+template <int DT>
+bool launch_bwd_slice_dt(int vec, int bm, const void* u, const void* zs, void* dzdx,
+                         const TileGeom& g, int R, const SliceArgs& sa, const BwdParams& prm,
+                         hipStream_t st);
+extern template bool launch_fwd_slice_dt<IABN_F32>(int, int, void*, const TileGeom&, int,
+                                                 const SliceArgs&, const FwdParams&, hipStream_t);
+extern template bool launch_bwd_slice_dt<IABN_F32>(int, int, const void*, const void*, void*,
+                                                 const TileGeom&, int, const SliceArgs&,
+                                                 const BwdParams&, hipStream_t);
+extern template bool launch_fwd_slice_dt<IABN_F16>(int, int, void*, const TileGeom&, int,
+                                                 const SliceArgs&, const FwdParams&, hipStream_t);
+extern template bool launch_bwd_slice_dt<IABN_F16>(int, int, const void*, const void*, void*,
+                                                 const TileGeom&, int, const SliceArgs&,
+                                                 const BwdParams&, hipStream_t);
+extern template bool launch_fwd_slice_dt<IABN_BF16>(int, int, void*, const TileGeom&, int,
+                                                 const SliceArgs&, const FwdParams&, hipStream_t);
+extern template bool launch_bwd_slice_dt<IABN_BF16>(int, int, const void*, const void*, void*,
+                                                 const TileGeom&, int, const SliceArgs&,
+                                                 const BwdParams&, hipStream_t);
+
+inline bool launch_fwd_slice(int dtype, int vec, int fm, void* xz, const TileGeom& g, int R,
+                             const SliceArgs& sa, const FwdParams& prm, hipStream_t st) {
+    return dtype == IABN_F32   ? launch_fwd_slice_dt<IABN_F32>(vec, fm, xz, g, R, sa, prm, st)
+           : dtype == IABN_F16 ? launch_fwd_slice_dt<IABN_F16>(vec, fm, xz, g, R, sa, prm, st)
+                               : launch_fwd_slice_dt<IABN_BF16>(vec, fm, xz, g, R, sa, prm, st);
+}
+
+inline bool launch_bwd_slice(int dtype, int vec, int bm, const void* u, const void* zs, void* dzdx,
+                             const TileGeom& g, int R, const SliceArgs& sa, const BwdParams& prm,
+                             hipStream_t st) {
+    return dtype == IABN_F32   ? launch_bwd_slice_dt<IABN_F32>(vec, bm, u, zs, dzdx, g, R, sa, prm, st)
+           : dtype == IABN_F16 ? launch_bwd_slice_dt<IABN_F16>(vec, bm, u, zs, dzdx, g, R, sa, prm, st)
+                               : launch_bwd_slice_dt<IABN_BF16>(vec, bm, u, zs, dzdx, g, R, sa, prm, st);
+}
+
+// Accesses per thread (of each tensor) that the slice-resident kernels are
+// built to hold: in registers, the last rung also in LDS; the narrow ones
+// (accesses below 16 bytes) up to 16.
+constexpr int kSliceFwdRungs[] = {4, 8, 16, 20, 24, 32, 50};
+constexpr int kSliceBwdRungs[] = {4, 8, 16, 20, 24, 32};
+constexpr int kSliceNarrowRungs[] = {4, 8, 16};
+
 // False if no kernel is built for the plan's (T, R) (a planning bug).
 bool launch_fwd_fused(int dtype, int fm, void* xz, const Geom& g, const FusedPlan& fp,
                       const FwdParams& prm, hipStream_t st);

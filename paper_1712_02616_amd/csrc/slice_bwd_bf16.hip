@@ -1,0 +1,9 @@
+// The slice-resident backward kernels for bf16 storage.
+#include "slice_bwd.h"
+
+namespace iabn_impl {
+
+template bool launch_bwd_slice_dt<IABN_BF16>(int, int, const void*, const void*, void*, const TileGeom&,
+                                            int, const SliceArgs&, const BwdParams&, hipStream_t);
+
+}  // namespace iabn_impl

@@ -9,8 +9,9 @@
 //                slice) partial sums of dy and dy*w (see the backward modes)
 //   bwd_apply    combines the partial sums, writes dgamma/dbeta, overwrites
 //                dz with dx
-// They serve the phase entry points, and the fused entry points for shapes
-// the channel-resident kernels do not take (few channels, odd rows).
+// They serve the phase entry points, and the training entry points for
+// shapes that neither the channel-resident nor the slice-resident kernels
+// take (few channels with little data, many narrow accesses).
 //
 // Work decomposition.  A channel's m = N*HW values are N rows of HW
 // contiguous elements, C*HW elements apart.  Each channel is cut into P

@@ -1,0 +1,158 @@
+"""The slice-resident kernels at the sizes where they can go wrong: each rung
+of registers and what lies past it, tiles of whole rows and of parts of rows,
+ragged rows with every tail, unaligned tensors, channels cut into slices that
+exchange their sums (also when a block gives up waiting, in a library built
+to wait for one poll only), workspaces full of garbage, graph replays and
+concurrent streams.  Each shape goes through the parity checks of
+test_gpu_random_shapes.py (oracle, guard bands), InPlace-ABN I and II and both
+comparison blocks.
+"""
+
+from __future__ import annotations
+
+import ctypes
+import os
+
+import pytest
+import torch
+
+import paper_1712_02616_amd as iabn
+import test_gpu_graph
+import test_gpu_random_shapes as parity
+import test_gpu_streams
+from gpu_helpers import TORCH_DTYPES, say
+from paper_1712_02616_amd import build as iabn_build
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a HIP GPU")]
+
+
+def _shape(N, C, HW, dtype, offset=0):
+    name = "%s_n%d_c%d_hw%d_o%d" % (dtype, N, C, HW, offset)
+    return parity.Shape(name, N, C, HW, dtype, offset, 9000 + (N * 31 + C * 7 + HW) % 1000)
+
+
+# One row of J * 1024 + 1 fp32 values in 257 channels: one slice of J 16-byte
+# accesses per thread (the last ones of each rung, and the first past it).
+RUNGS = [_shape(1, 257, J * 1024 + 1, "f32") for J in (4, 5, 9, 17, 21, 25, 33, 51)]
+# Tails of 1 to 7 elements, tiles of parts of rows.
+TAILS = [_shape(3, 40, 2048 + k, dt) for dt, ks in (("f16", (1, 2, 3, 5, 6, 7)), ("f32", (1, 2, 3)))
+         for k in ks]
+SMALL = [
+    _shape(2, 16, 64, "f32"),           # less than a tile
+    _shape(100, 300, 71, "f16"),        # whole rows per tile, the last tile with fewer; long tails
+    _shape(37, 270, 115, "bf16"),
+    _shape(5, 7, 1041, "bf16"),
+    _shape(64, 5, 196, "f16"),          # 8-byte accesses
+    _shape(9, 11, 50, "f16"),           # 4-byte accesses, rows shorter than a line
+    _shape(40, 33, 49, "f16"),          # 2-byte accesses
+    _shape(4, 30, 4096, "f16", 1),      # whole accesses at an element's alignment
+    _shape(4, 30, 4096, "f32", 3),
+]
+# Channels cut into P slices (few, many, the most) that exchange sums.
+EXCHANGE = [
+    _shape(4, 40, 40000, "f16"),        # 12 slices
+    _shape(2, 90, 66000, "f16"),        # 5
+    _shape(3, 4, 524289, "f16"),        # 64, a tail
+    _shape(2, 200, 25001, "bf16"),      # 2
+    _shape(6, 20, 50176, "f32"),        # 25
+]
+CHECKS = [parity.test_random_shape_parity, parity.test_random_shape_backward_ii,
+          parity.test_random_shape_standard_block, parity.test_random_shape_checkpointing]
+ID = lambda v: v.id if isinstance(v, parity.Shape) else v.__name__.replace("test_random_shape_", "")  # noqa: E731
+
+
+@pytest.mark.parametrize("s", EXCHANGE + RUNGS, ids=ID)
+def test_takes_the_slices(s):
+    for op in ("forward_train", "backward"):
+        p = iabn.iabn_plan(op, TORCH_DTYPES[s.dtype], s.N, s.C, s.HW)
+        P = max(1, min(512 // s.C, 64))
+        assert p["channel_resident"] == 0 and p["access_bytes"] == 16, p
+        assert p["blocks"] == s.C * P, p
+
+
+@pytest.mark.parametrize("check", CHECKS, ids=ID)
+@pytest.mark.parametrize("s", TAILS + SMALL + EXCHANGE, ids=ID)
+def test_slices(s, check):
+    check(s)
+
+
+@pytest.mark.parametrize("check", CHECKS[:1] + CHECKS[2:3], ids=ID)
+@pytest.mark.parametrize("s", RUNGS, ids=ID)
+def test_rungs(s, check):
+    check(s)
+
+
+@pytest.fixture
+def abandoning(monkeypatch):
+    """The binding on the library whose fp16 slices wait for one poll only."""
+    if not os.path.exists(iabn_build.ABANDON_LIB):
+        iabn_build.build()
+    monkeypatch.setattr(iabn, "_lib", iabn.declare(ctypes.CDLL(iabn_build.ABANDON_LIB)))
+
+
+@pytest.mark.parametrize("check", CHECKS, ids=ID)
+@pytest.mark.parametrize("s", [s for s in EXCHANGE if s.dtype == "f16"], ids=ID)
+def test_abandoned_slices(s, check, abandoning):
+    check(s)
+
+
+GRAPH = ((4, 40, 40000), "f16")
+
+
+def test_graph_replay():
+    test_gpu_graph.test_graph_replay_matches_eager(*GRAPH)
+
+
+def test_graph_replay_ragged():
+    test_gpu_graph.test_graph_replay_matches_eager((2, 100, 30003), "f16")
+
+
+def test_graph_replay_abandoned(abandoning):
+    test_gpu_graph.test_graph_replay_matches_eager(*GRAPH)
+
+
+def _results(L):
+    s = torch.cuda.current_stream()
+    test_gpu_streams._run(L, s)
+    torch.cuda.synchronize()
+    return {k: L[k].clone() for k in ("x", "dz", "rm", "rv", "sm", "sv", "dg", "db")}
+
+
+def test_workspace_content_does_not_matter():
+    """Zeros, ones in every bit, random bytes, what other calls left: the same bits come out."""
+    L = test_gpu_streams._layer((4, 40, 40000), "f16", 94)
+    L["ws"].zero_()
+    ref = _results(L)
+    for what in ("ones", "random", "phases", "again"):
+        say("workspace: %s" % what)
+        if what == "ones":
+            L["ws"].fill_(255)
+        elif what == "random":
+            L["ws"].random_(0, 256)
+        elif what == "phases":
+            iabn.iabn_forward_stats(L["x0"], L["ws"])
+        got = _results(L)
+        for k, v in ref.items():
+            assert torch.equal(got[k], v), (what, k)
+
+
+def test_concurrent_streams():
+    """Layers on four streams at once (their blocks do not all fit the chip)
+    give what they give one after the other."""
+    layers = [test_gpu_streams._layer((4, 40, 40000), "f16", 95 + i) for i in range(3)]
+    layers.append(test_gpu_streams._layer((2, 100, 30003), "f32", 99))
+    ref = [_results(L) for L in layers]
+    s0 = torch.cuda.current_stream()
+    for rep in range(3):
+        say("concurrent %d" % rep)
+        streams = [torch.cuda.Stream() for _ in layers]
+        for L, s in zip(layers, streams):
+            s.wait_stream(s0)
+            test_gpu_streams._run(L, s)
+        for s in streams:
+            s0.wait_stream(s)
+        torch.cuda.synchronize()
+        for L, r in zip(layers, ref):
+            for k, v in r.items():
+                assert torch.equal(L[k], v), k
