@@ -7,6 +7,10 @@ shape and the current HIP stream, and turns a nonzero status into
 ``IabnError``.  All arithmetic happens in the HIP kernels of ``libiabn.so``;
 there is no other code path, and calls fail if the library cannot be loaded.
 
+The plain case of the entry points (plain tensors, torch's current stream)
+is marshalled by native code (``binding.cpp``); where that declines, the
+function's Python code does the same checks and reports what is wrong.
+
 Tensors: activations/gradients are contiguous NCHW (any number of trailing
 spatial dims, flattened to HW) in float32, float16 or bfloat16 on a HIP
 device; per-channel tensors are contiguous float32 of length C on the same
@@ -17,6 +21,7 @@ stream for the tensor's device).
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import math
 import threading
 
@@ -51,6 +56,14 @@ class _Plan(ctypes.Structure):
 _lib = None
 _lib_lock = threading.Lock()
 
+# The native calls' table of entry points (binding.cpp: Op); an op is an index.
+_NATIVE = ("iabn_workspace_size", "iabn_forward_train", "iabn_forward_train_noalloc",
+           "iabn_forward_eval", "iabn_backward", "iabn_backward_ii", "iabn_std_forward_train",
+           "iabn_std_backward", "iabn_ckpt_forward_train", "iabn_ckpt_recompute",
+           "iabn_ckpt_backward")
+(_WORKSPACE_SIZE, _FORWARD_TRAIN, _FORWARD_TRAIN_NOALLOC, _FORWARD_EVAL, _BACKWARD, _BACKWARD_II,
+ _STD_FORWARD, _STD_BACKWARD, _CKPT_FORWARD, _CKPT_RECOMPUTE, _CKPT_BACKWARD) = range(len(_NATIVE))
+
 
 class IabnError(RuntimeError):
     """A libiabn entry point returned a nonzero status."""
@@ -73,6 +86,7 @@ def load():
         if _lib is None:
             if not _build.is_built():
                 _build.build()
+                _build.build_binding()
             _lib = declare(ctypes.CDLL(_build.LIB))
     return _lib
 
@@ -105,7 +119,41 @@ def declare(lib):
         fn = getattr(lib, name)
         fn.argtypes = args
         fn.restype = res
+    lib.table_array = (ctypes.c_void_p * len(_NATIVE))(
+        *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE))
+    lib.table = ctypes.addressof(lib.table_array)
     return lib
+
+
+def _first_call(*args):
+    """Loads the native fast path (building it first if it has never been
+    built) and calls it."""
+    global _call
+    with _lib_lock:
+        if _call is _first_call:
+            if not _build.is_built():
+                _build.build()
+                _build.build_binding()
+            spec = importlib.util.spec_from_file_location(__name__ + "._binding", _build.BINDING_LIB)
+            module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(module)
+            _call = module.call
+    return _call(*args)
+
+
+# call(table, op, tensors..., floats...[, workspace]) -> status, or
+# NotImplemented where it is not the plain case.
+_call = _first_call
+
+
+def _native(name, op, *args):
+    """Whether the native call did it (and succeeded)."""
+    rc = _call((_lib or load()).table, op, *args)
+    if rc is NotImplemented:
+        return False
+    if rc:
+        _check(name, rc)
+    return True
 
 
 def _check(name: str, rc: int) -> None:
@@ -197,6 +245,9 @@ def iabn_plan(op, dtype, N: int, C: int, HW: int) -> dict:
 def iabn_forward_train(x_z, gamma, beta, running_mean, running_var, save_mean, save_var,
                        eps=1e-5, momentum=0.1, slope=0.01, workspace=None, stream=None):
     """Training forward (Algorithm 1), in place over ``x_z``; returns ``x_z``."""
+    if stream is None and _native("iabn_forward_train", _FORWARD_TRAIN, x_z, gamma, beta, running_mean, running_var,
+                                   save_mean, save_var, eps, momentum, slope, workspace):
+        return x_z
     N, C, HW = _nchw(x_z, "x_z")
     code = DTYPE_CODES[x_z.dtype]
     dev = x_z.device
@@ -214,6 +265,9 @@ def iabn_forward_train_noalloc(x_z, gamma, beta, running_mean, running_var, save
                                eps=1e-5, momentum=0.1, slope=0.01, stream=None):
     """iabn_forward_train with the library's static scratch in place of a
     workspace (no allocation, here or in the library); returns ``x_z``."""
+    if stream is None and _native("iabn_forward_train_noalloc", _FORWARD_TRAIN_NOALLOC, x_z, gamma, beta,
+                                   running_mean, running_var, save_mean, save_var, eps, momentum, slope):
+        return x_z
     N, C, HW = _nchw(x_z, "x_z")
     code = DTYPE_CODES[x_z.dtype]
     dev = x_z.device
@@ -229,6 +283,9 @@ def iabn_forward_train_noalloc(x_z, gamma, beta, running_mean, running_var, save
 def iabn_forward_eval(x_z, gamma, beta, running_mean, running_var, eps=1e-5, slope=0.01,
                       stream=None):
     """Inference forward with the running statistics, in place; returns ``x_z``."""
+    if stream is None and _native("iabn_forward_eval", _FORWARD_EVAL, x_z, gamma, beta, running_mean, running_var, eps,
+                                   slope):
+        return x_z
     N, C, HW = _nchw(x_z, "x_z")
     code = DTYPE_CODES[x_z.dtype]
     dev = x_z.device
@@ -243,6 +300,9 @@ def iabn_forward_eval(x_z, gamma, beta, running_mean, running_var, eps=1e-5, slo
 def iabn_backward(z, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps=1e-5, slope=0.01,
                   workspace=None, stream=None):
     """Backward (Algorithm 2, InPlace-ABN I), in place over ``dz_dx``; returns ``dz_dx``."""
+    if stream is None and _native("iabn_backward", _BACKWARD, z, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps, slope,
+                                   workspace):
+        return dz_dx
     N, C, HW = _nchw(z, "z")
     if _nchw(dz_dx, "dz_dx") != (N, C, HW) or dz_dx.dtype != z.dtype or dz_dx.device != z.device:
         raise ValueError("dz_dx must match z in shape, dtype and device")
@@ -267,6 +327,9 @@ def _same(a, b, what_a, what_b):
 def iabn_backward_ii(z, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps=1e-5, slope=0.01,
                      workspace=None, stream=None):
     """Backward with InPlace-ABN II (gradients in terms of y), in place over ``dz_dx``."""
+    if stream is None and _native("iabn_backward_ii", _BACKWARD_II, z, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps,
+                                   slope, workspace):
+        return dz_dx
     N, C, HW = _same(z, dz_dx, "z", "dz_dx")
     code = DTYPE_CODES[z.dtype]
     dev = z.device
@@ -282,6 +345,9 @@ def iabn_backward_ii(z, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps=1e-5, s
 def iabn_std_forward_train(x, z, gamma, beta, running_mean, running_var, save_mean, save_var,
                            eps=1e-5, momentum=0.1, slope=0.01, workspace=None, stream=None):
     """Standard block forward: ``x`` kept, ``z`` written; returns ``z``."""
+    if stream is None and _native("iabn_std_forward_train", _STD_FORWARD, x, z, gamma, beta, running_mean,
+                                   running_var, save_mean, save_var, eps, momentum, slope, workspace):
+        return z
     N, C, HW = _same(x, z, "x", "z")
     code = DTYPE_CODES[x.dtype]
     dev = x.device
@@ -298,6 +364,9 @@ def iabn_std_forward_train(x, z, gamma, beta, running_mean, running_var, save_me
 def iabn_std_backward(x, z, dz_dx, gamma, beta, save_mean, save_var, dgamma, dbeta, eps=1e-5,
                       slope=0.01, workspace=None, stream=None):
     """Standard block backward from ``x`` (and the signs of ``z``), in place over ``dz_dx``."""
+    if stream is None and _native("iabn_std_backward", _STD_BACKWARD, x, z, dz_dx, gamma, beta, save_mean, save_var,
+                                   dgamma, dbeta, eps, slope, workspace):
+        return dz_dx
     N, C, HW = _same(x, z, "x", "z")
     _same(x, dz_dx, "x", "dz_dx")
     code = DTYPE_CODES[x.dtype]
@@ -315,6 +384,9 @@ def iabn_ckpt_forward_train(x_xhat, z, gamma, beta, running_mean, running_var, s
                             save_var, eps=1e-5, momentum=0.1, slope=0.01, workspace=None,
                             stream=None):
     """Checkpointing forward: xhat over ``x_xhat``, ``z`` written; returns ``z``."""
+    if stream is None and _native("iabn_ckpt_forward_train", _CKPT_FORWARD, x_xhat, z, gamma, beta, running_mean,
+                                   running_var, save_mean, save_var, eps, momentum, slope, workspace):
+        return z
     N, C, HW = _same(x_xhat, z, "x_xhat", "z")
     code = DTYPE_CODES[x_xhat.dtype]
     dev = x_xhat.device
@@ -331,6 +403,8 @@ def iabn_ckpt_forward_train(x_xhat, z, gamma, beta, running_mean, running_var, s
 
 def iabn_ckpt_recompute(xhat, z, gamma, beta, slope=0.01, stream=None):
     """z = f(gamma*xhat + beta) from the stored xhat; returns ``z``."""
+    if stream is None and _native("iabn_ckpt_recompute", _CKPT_RECOMPUTE, xhat, z, gamma, beta, slope):
+        return z
     N, C, HW = _same(xhat, z, "xhat", "z")
     code = DTYPE_CODES[xhat.dtype]
     dev = xhat.device
@@ -345,6 +419,9 @@ def iabn_ckpt_recompute(xhat, z, gamma, beta, slope=0.01, stream=None):
 def iabn_ckpt_backward(xhat, dz_dx, gamma, beta, save_var, dgamma, dbeta, eps=1e-5, slope=0.01,
                        workspace=None, stream=None):
     """Checkpointing backward from the stored xhat, in place over ``dz_dx``."""
+    if stream is None and _native("iabn_ckpt_backward", _CKPT_BACKWARD, xhat, dz_dx, gamma, beta, save_var, dgamma, dbeta,
+                                   eps, slope, workspace):
+        return dz_dx
     N, C, HW = _same(xhat, dz_dx, "xhat", "dz_dx")
     code = DTYPE_CODES[xhat.dtype]
     dev = xhat.device

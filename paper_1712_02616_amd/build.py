@@ -25,6 +25,8 @@ LIB = os.path.join(HERE, "libiabn.so")
 ABANDON_LIB = os.path.join(HERE, "libiabn_abandon.so")
 ABANDON_SOURCES = ("slice_fwd_f16.hip", "slice_bwd_f16.hip")
 ABANDON_FLAG = "-DIABN_SLICE_POLLS=1"
+BINDING_SRC = os.path.join(HERE, "binding.cpp")
+BINDING_LIB = os.path.join(HERE, "_binding.so")
 PROBE_SRC = os.path.join(HERE, "bench_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libiabn_probe.so")
 ARCH = "gfx950"
@@ -83,6 +85,32 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_binding() -> str:
+    """Always recompiles _binding.so (the Python binding's fast path, host
+    code against torch's and Python's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    incs = [os.path.join(ROOT, "include"), os.path.join(rocm, "include"),
+            sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
+    out = BINDING_LIB + ".tmp%d" % os.getpid()
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = (["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-o", out, BINDING_SRC] +
+           [a for i in incs for a in ("-isystem", i)] +
+           ["-L", libs, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-Wl,-rpath," + libs])
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building the binding failed (%d):\n%s\n%s"
+                           % (res.returncode, " ".join(cmd), res.stderr))
+    os.replace(out, BINDING_LIB)
+    return BINDING_LIB
+
+
 def build_probe() -> str:
     """Always recompiles libiabn_probe.so (the benchmark's bandwidth probes)."""
     out = PROBE_LIB + ".tmp%d" % os.getpid()
@@ -95,9 +123,10 @@ def build_probe() -> str:
 
 
 def is_built() -> bool:
-    return os.path.exists(LIB)
+    return os.path.exists(LIB) and os.path.exists(BINDING_LIB)
 
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_binding())
     print(build_probe())
