@@ -243,6 +243,36 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     return C >= kFusedMinChannels || (vec * eb == 16 && J <= kOneSliceMaxJ);
 }
 
+// The passes without a reduction by tiles (pointwise_kernel), or false where
+// the general mapping is the better choice (us, before -> after): ragged rows
+// always (inference (8, 256, 129x129) fp16 36.3 -> 32.3, (8, 512, 65x65) 19.0
+// -> 18.2, (16, 300, 33x33) fp32 12.5 -> 11.5; the recomputation 143 -> 32.3,
+// 73 -> 18.3, 24.8 -> 11.7); of the other rows the recomputation in 16-byte
+// accesses, with fewer channels than kPointMaxChannels (each is then cut into
+// slices or has a long one) and kPointMinJ accesses per thread ((8, 256,
+// 128x128) fp16 30.8 -> 26.1, (8, 64, 256x256) 32.4 -> 25.6, (32, 256, 56x56)
+// fp32 43.0 -> 36.3; but (8, 1024, 64x64) 24.2 -> 25.0, (16, 2048, 28x28)
+// 22.0 -> 22.3, (2, 16, 8x8) 2.1 -> 2.2).
+constexpr int64_t kPointMaxChannels = 1024;
+constexpr int64_t kPointMinJ = 4;
+
+bool plan_pointwise(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool recompute,
+                    SlicePlan* out) {
+    const bool ragged = ragged_rows(HW, eb, vec);
+    if (!ragged && (!recompute || vec * eb != 16 || C >= kPointMaxChannels)) return false;
+    out->vec = 16 / eb;
+    TileGeom a, b;
+    const bool ok64 = make_tiles(N, C, HW, eb, out->vec, 64, &a);
+    const bool ok256 = make_tiles(N, C, HW, eb, out->vec, kThreads, &b);
+    if (!ok64 && !ok256) return false;
+    const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
+    const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
+    out->g = slots64 < slots256 ? a : b;
+    set_slices(&out->g,
+               split_channel(N * HW, C, recompute ? kTargetBlocks : eval_target_blocks(C)).P);
+    return ragged || out->g.tiles >= kPointMinJ * out->g.step;
+}
+
 // Workspace bytes a slice-resident launch uses.
 size_t slice_workspace(const SlicePlan& p) {
     return p.g.P > 1 ? static_cast<size_t>(p.g.C) * p.g.P * kSliceWords * sizeof(uint64_t) : 0;
@@ -559,6 +589,8 @@ int iabn_plan(int op, int dtype, int64_t N, int64_t C, int64_t HW, iabn_plan_t* 
         plan->threads = kThreads;
         plan->blocks = C * static_cast<int64_t>(route == Route::kSlice ? sl.g.P : g.P);
         if (route == Route::kSlice) plan->access_bytes = sl.vec * eb;
+        if (!train && plan_pointwise(N, C, HW, eb, vec, op == IABN_OP_CKPT_RECOMPUTE, &sl))
+            plan->access_bytes = sl.vec * eb;
     }
     return ok();
 }
@@ -651,8 +683,12 @@ int iabn_forward_eval(void* x_z, int dtype, const float* gamma, const float* bet
     const FwdParams prm = {gamma, beta, const_cast<float*>(running_mean),
                            const_cast<float*>(running_var), nullptr, nullptr, nullptr, eps, 0.f,
                            slope};
-    launch_fwd_apply(dtype, vec, x_z, g, static_cast<const Partial*>(nullptr), prm, false,
-                     kFwdInPlace, static_cast<hipStream_t>(stream));
+    SlicePlan pw;
+    if (plan_pointwise(N, C, HW, elem_bytes(dtype), vec, false, &pw))
+        launch_pointwise(dtype, x_z, x_z, pw.g, prm, false, static_cast<hipStream_t>(stream));
+    else
+        launch_fwd_apply(dtype, vec, x_z, g, static_cast<const Partial*>(nullptr), prm, false,
+                         kFwdInPlace, static_cast<hipStream_t>(stream));
     return launched("fwd_eval");
 }
 
@@ -751,8 +787,14 @@ int iabn_ckpt_recompute(const void* xhat, void* z, int dtype, const float* gamma
         return fail(IABN_ERR_NULL, "a tensor or parameter pointer is NULL");
     if ((rc = check_params(1.f, slope))) return rc;
     const int vec = access_vec(HW, dtype, xhat, z, nullptr);
-    const Geom g = make_geom(N, C, HW, dtype, vec);
-    launch_recompute(dtype, vec, xhat, z, g, gamma, beta, slope, static_cast<hipStream_t>(stream));
+    SlicePlan pw;
+    if (plan_pointwise(N, C, HW, elem_bytes(dtype), vec, true, &pw)) {
+        const FwdParams prm = {gamma, beta, nullptr, nullptr, nullptr, nullptr, z, 1.f, 0.f, slope};
+        launch_pointwise(dtype, xhat, z, pw.g, prm, true, static_cast<hipStream_t>(stream));
+    } else {
+        const Geom g = make_geom(N, C, HW, dtype, vec);
+        launch_recompute(dtype, vec, xhat, z, g, gamma, beta, slope, static_cast<hipStream_t>(stream));
+    }
     return launched("recompute");
 }
 

@@ -26,6 +26,11 @@ void launch_bwd_apply(int dtype, int vec, const void* u, const void* zs, void* d
 void launch_recompute(int dtype, int vec, const void* xhat, void* z, const Geom& g,
                       const float* gamma, const float* beta, float slope, hipStream_t st);
 
+// The recomputation or the inference forward by tiles of 16-byte accesses.
+struct TileGeom;  // tile.h
+void launch_pointwise(int dtype, const void* src, void* dst, const TileGeom& g,
+                      const FwdParams& prm, bool recompute, hipStream_t st);
+
 // ---- channel-resident kernels (fused_fwd.hip, fused_bwd.hip)
 
 // Used when every channel gets a block of its own and at least one block per
@@ -209,7 +214,6 @@ inline bool fused_strips(const Geom& g, const FusedPlan& fp, bool wide) {
 
 // ---- slice-resident kernels (slice_fwd.h, slice_bwd.h)
 
-struct TileGeom;   // tile.h
 struct SliceArgs;  // tile.h
 
 // False if no kernel is built for the access width and R (a planning bug).

@@ -13,14 +13,17 @@ from __future__ import annotations
 import ctypes
 import os
 
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1712_02616_amd as iabn
 import test_gpu_graph
 import test_gpu_random_shapes as parity
 import test_gpu_streams
-from gpu_helpers import TORCH_DTYPES, say
+import workloads
+from gpu_helpers import TORCH_DTYPES, assert_close, say, to_f64
 from paper_1712_02616_amd import build as iabn_build
 
 pytestmark = [pytest.mark.gpu,
@@ -81,6 +84,30 @@ def test_slices(s, check):
 @pytest.mark.parametrize("s", RUNGS, ids=ID)
 def test_rungs(s, check):
     check(s)
+
+
+@pytest.mark.parametrize("s", TAILS + SMALL + EXCHANGE[2:4], ids=ID)
+def test_inference(s):
+    """The inference forward on the same rows (ragged ones by tiles too)."""
+    inp = workloads.make_layer(s.N, s.C, s.HW, s.dtype, s.seed, gamma_sign=True)
+    rm = np.linspace(-1.5, 1.5, s.C).astype(np.float32)
+    rv = np.linspace(0.3, 4.0, s.C).astype(np.float32)
+    buf, x = parity._placed(inp.x, s.dtype, s.offset, 5.5)
+    iabn.iabn_forward_eval(x, *(torch.from_numpy(v).cuda() for v in (inp.gamma, inp.beta, rm, rv)),
+                           1e-5, 0.01)
+    torch.cuda.synchronize()
+    ref = oracle.forward_eval(workloads.storage_to_f64(inp.x, s.dtype), inp.gamma, inp.beta, rm, rv,
+                              parity.F32(1e-5), parity.F32(0.01))
+    assert_close("z", to_f64(x), ref, s.dtype)
+    assert parity._untouched(buf, s.offset, s.N * s.C * s.HW, 5.5)
+
+
+# The recomputation's rules: few and many accesses per thread, few and many
+# channels, against the general mapping's arithmetic (the forward's z).
+@pytest.mark.parametrize("s", [_shape(8, 64, 4096, "f16"), _shape(2, 40, 20000, "bf16"),
+                               _shape(2, 1030, 2048, "f16"), _shape(5, 1020, 1024, "f32")], ids=ID)
+def test_recomputation(s):
+    parity.test_random_shape_checkpointing(s)
 
 
 @pytest.fixture
