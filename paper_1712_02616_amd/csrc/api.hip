@@ -110,11 +110,47 @@ struct SlicePlan {
     int R;    // accesses per thread the kernel holds
 };
 
+// Rows of at least a cache line that only 2- or 4-byte accesses divide (or
+// tensors aligned to no more) move in 16-byte accesses at element alignment
+// (ragged rows, tile.h).
+constexpr int64_t kRaggedMinRowBytes = kLineBytes;
+// Channels of more values than this take the slice-resident kernels where
+// rows are ragged; smaller ones fit the channel-resident kernels' narrow
+// accesses, whose code is shorter: (8, 512, 21x21) fp16 (3528 values) 6.4 /
+// 7.9 us against 5.6 / 6.3, (8, 1024, 27x27) (5832) 10.4 / 13.9 against 12.0
+// / 15.0, (8, 512, 65x65) 16.7 / 23.2 against 28.3 / 38.0, (8, 256, 129x129)
+// 32.6 / 42.3 against 115 / 143.
+constexpr int64_t kRaggedMinChannel = 4096;
+
+// Rows that 8-byte accesses divide do so only in channels larger than the
+// registers of the largest narrow channel-resident block: (8, 256, 16644)
+// fp16 forward 34.4 -> 33.5 us, backward 49.2 -> 42.7, (64, 64, 110x110) 58.6
+// -> 44.7 and 86.8 -> 62.9.
+constexpr int64_t kRaggedMinAccesses8 = 16384;
+
+// Rows aligned to no more than 2 bytes whose accesses start at a 16-byte
+// boundary (tile.h): of at least kHeadsMinRow elements, so that the edges
+// stay few.  Forward / backward us, at the alignment of an element -> at the
+// boundary: (8, 512, 65x65) fp16 20.9 / 30.3 -> 16.6 / 23.3, (16, 300, 33x33)
+// fp16 13.9 / 20.9 -> 11.6 / 15.3; aligned to 4 bytes it gains nothing ((16,
+// 300, 33x33) fp32 12.9 / 17.8 -> 13.2 / 18.6).
+constexpr int64_t kHeadsMinRow = 512;
+
+bool row_heads(int64_t HW, int eb, int vec) { return vec * eb == 2 && HW >= kHeadsMinRow; }
+
+bool ragged_rows(int64_t N, int64_t HW, int eb, int vec) {
+    if (HW * eb < kRaggedMinRowBytes) return false;
+    return vec * eb <= 4 || (vec * eb == 8 && N * HW / vec > kRaggedMinAccesses8);
+}
+
 // The tiles of a layer for accesses of `vec` elements (tile.h) by groups of
 // `lanes` threads.  False where a tile does not fit 32-bit byte offsets.
-bool make_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, int lanes, TileGeom* g) {
+bool make_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, int lanes, bool heads,
+                TileGeom* g) {
     const int64_t ab = static_cast<int64_t>(vec) * eb, row = HW * eb, nstride = C * row;
-    const int64_t vrow = HW / vec, tail = HW % vec, limit = int64_t(1) << 30;
+    const int64_t limit = int64_t(1) << 30;
+    // (With any head the accesses stay in the row.)
+    const int64_t vrow = heads ? (HW - (vec - 1)) / vec : HW / vec, edge = HW - vrow * vec;
     if (vrow < 1 || row >= limit) return false;
     g->C = static_cast<uint32_t>(C);
     g->lanes = static_cast<uint32_t>(lanes);
@@ -134,10 +170,11 @@ bool make_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, int lanes, Ti
     g->wrap_at = g->split_rows ? static_cast<uint32_t>(per * lanes * ab) : UINT32_MAX;
     g->row_bytes = static_cast<uint64_t>(row);
     g->nstride = static_cast<uint64_t>(nstride);
-    g->tail = static_cast<uint32_t>(tail);
-    g->tail_div = iabn_divmagic_make(tail ? g->tail : 1u);
-    g->tails = static_cast<uint32_t>(N * tail);
-    g->tail_at = static_cast<uint32_t>(vrow * ab);
+    g->head_mask = heads ? 15u : 0u;
+    g->edge = static_cast<uint32_t>(edge);
+    g->edge_div = iabn_divmagic_make(edge ? g->edge : 1u);
+    g->edges = static_cast<uint32_t>(N * edge);
+    g->body_bytes = static_cast<uint32_t>(vrow * ab);
     g->xcd_order = row % kLineBytes != 0 ? 1u : 0u;
     g->m = static_cast<double>(N) * static_cast<double>(HW);
     g->inv_m = 1.0 / g->m;
@@ -155,22 +192,6 @@ void set_slices(TileGeom* g, int64_t P) {
         g->step_at = 0;
         g->step_base = static_cast<uint64_t>(g->step) * g->per * g->nstride;
     }
-}
-
-// Rows of at least a cache line that only 2- or 4-byte accesses divide (or
-// tensors aligned to no more) move in 16-byte accesses at element alignment
-// (ragged rows, tile.h).
-constexpr int64_t kRaggedMinRowBytes = kLineBytes;
-// Channels of more values than this take the slice-resident kernels where
-// rows are ragged; smaller ones fit the channel-resident kernels' narrow
-// accesses, whose code is shorter: (8, 512, 21x21) fp16 (3528 values) 6.4 /
-// 7.9 us against 5.6 / 6.3, (8, 1024, 27x27) (5832) 10.4 / 13.9 against 12.0
-// / 15.0, (8, 1024, 65x65) 38.9 / 53.7 against 55.3 / 70.9, (8, 256, 129x129)
-// 35.5 / 51.0 against 115 / 143.
-constexpr int64_t kRaggedMinChannel = 4096;
-
-bool ragged_rows(int64_t HW, int eb, int vec) {
-    return vec * eb <= 4 && HW * eb >= kRaggedMinRowBytes;
 }
 
 // Blocks of the slice-resident kernels that the chip holds at once: two per
@@ -209,12 +230,13 @@ constexpr int64_t kSliceNarrowMaxJ = 32;
 // Ragged rows take them whatever their size (the channel-resident and the
 // streaming kernels would move them in 2- or 4-byte accesses).
 bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward, SlicePlan* out) {
-    const bool ragged = ragged_rows(HW, eb, vec);
+    const bool ragged = ragged_rows(N, HW, eb, vec);
+    const bool heads = ragged && row_heads(HW, eb, vec);
     const int v = ragged ? 16 / eb : vec;
     const bool wide = v * eb == 16;
     TileGeom a, b;
-    const bool ok64 = make_tiles(N, C, HW, eb, v, 64, &a);
-    const bool ok256 = make_tiles(N, C, HW, eb, v, kThreads, &b);
+    const bool ok64 = make_tiles(N, C, HW, eb, v, 64, heads, &a);
+    const bool ok256 = make_tiles(N, C, HW, eb, v, kThreads, heads, &b);
     if (!ok64 && !ok256) return false;
     const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
     const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
@@ -245,9 +267,9 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
 
 // The passes without a reduction by tiles (pointwise_kernel), or false where
 // the general mapping is the better choice (us, before -> after): ragged rows
-// always (inference (8, 256, 129x129) fp16 36.3 -> 32.3, (8, 512, 65x65) 19.0
-// -> 18.2, (16, 300, 33x33) fp32 12.5 -> 11.5; the recomputation 143 -> 32.3,
-// 73 -> 18.3, 24.8 -> 11.7); of the other rows the recomputation in 16-byte
+// always (inference (8, 256, 129x129) fp16 36.3 -> 31.1, (8, 512, 65x65) 19.0
+// -> 18.0, (16, 300, 33x33) fp32 12.5 -> 11.5; the recomputation 143 -> 30.8,
+// 73 -> 18.2, 24.8 -> 11.9); of the other rows the recomputation in 16-byte
 // accesses, with fewer channels than kPointMaxChannels (each is then cut into
 // slices or has a long one) and kPointMinJ accesses per thread ((8, 256,
 // 128x128) fp16 30.8 -> 26.1, (8, 64, 256x256) 32.4 -> 25.6, (32, 256, 56x56)
@@ -258,12 +280,13 @@ constexpr int64_t kPointMinJ = 4;
 
 bool plan_pointwise(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool recompute,
                     SlicePlan* out) {
-    const bool ragged = ragged_rows(HW, eb, vec);
+    const bool ragged = ragged_rows(N, HW, eb, vec);
     if (!ragged && (!recompute || vec * eb != 16 || C >= kPointMaxChannels)) return false;
+    const bool heads = ragged && row_heads(HW, eb, vec);
     out->vec = 16 / eb;
     TileGeom a, b;
-    const bool ok64 = make_tiles(N, C, HW, eb, out->vec, 64, &a);
-    const bool ok256 = make_tiles(N, C, HW, eb, out->vec, kThreads, &b);
+    const bool ok64 = make_tiles(N, C, HW, eb, out->vec, 64, heads, &a);
+    const bool ok256 = make_tiles(N, C, HW, eb, out->vec, kThreads, heads, &b);
     if (!ok64 && !ok256) return false;
     const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
     const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
@@ -372,7 +395,7 @@ enum class Route { kChannel, kSlice, kStream };
 Route plan_route(int64_t N, int64_t C, int64_t HW, int dtype, const Geom& g, bool backward,
                  bool narrow_ok, FusedPlan* fp, SlicePlan* sl) {
     const int eb = elem_bytes(dtype), vec = static_cast<int>(g.vec);
-    if (ragged_rows(HW, eb, vec) && N * HW > kRaggedMinChannel &&
+    if (ragged_rows(N, HW, eb, vec) && N * HW > kRaggedMinChannel &&
         plan_slice(N, C, HW, eb, vec, backward, sl))
         return Route::kSlice;
     if (plan_fused(C, g, eb, backward, narrow_ok, fp)) return Route::kChannel;

@@ -6,7 +6,7 @@
 // Measured (backward us, before: two streaming passes, or narrow accesses):
 // (32, 64, 112x112) fp16 43.4 -> 33.6, (8, 64, 256x256) 55.2 -> 41.9 (3 b per
 // element at 4.8 TB/s), (8, 20, 224x224) bf16 21.6 -> 15.6, (8, 256, 129x129)
-// fp16 143 -> 51.0, (2, 16, 8x8) fp32 4.5 -> 3.6.
+// fp16 143 -> 42.3, (8, 512, 65x65) 38.0 -> 23.2, (2, 16, 8x8) fp32 4.5 -> 3.6.
 
 #pragma once
 
@@ -18,22 +18,22 @@ namespace {
 
 constexpr int kRestU = 2;  // accesses of each tensor in flight per thread past the resident ones
 
-// dx of the slice's accesses from j0 on and tail elements from i0 on, read
+// dx of the slice's accesses from j0 on and edge elements from i0 on, read
 // from memory.
 template <int DT, int VEC, int BM>
 __device__ __forceinline__ void apply_rest(const void* __restrict__ u, const void* __restrict__ zs,
                                            void* __restrict__ dzdx, const TileGeom& g, uint64_t chan,
-                                           const SliceTiles& s, uint32_t lane, uint32_t j0,
+                                           const SliceTiles& s, const TileLane& lane, uint32_t j0,
                                            uint32_t p, uint32_t i0,
                                            const BwdApplyElem<BM>& dx_of) {
     constexpr int EB = static_cast<int>(sizeof(typename Elem<DT>::T));
-    for (uint32_t i = i0; i < tail_rounds(g); ++i) {
-        const Tail t = tail_pos<EB>(g, chan, p, i);
+    for (uint32_t i = i0; i < edge_rounds(g); ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, p, i);
         if (!t.live) continue;
-        const float zv = BM == kBwdFromXZ ? static_cast<float>(tail_load<DT>(zs, t)) : 0.f;
-        tail_store<DT>(dzdx, t,
-                       dx_of(static_cast<float>(tail_load<DT>(u, t)), zv,
-                             static_cast<float>(tail_load<DT>(dzdx, t))));
+        const float zv = BM == kBwdFromXZ ? static_cast<float>(edge_load<DT>(zs, t)) : 0.f;
+        edge_store<DT>(dzdx, t,
+                       dx_of(static_cast<float>(edge_load<DT>(u, t)), zv,
+                             static_cast<float>(edge_load<DT>(dzdx, t))));
     }
     if (j0 >= s.count) return;
     TileWalk w = walk_begin(g, chan, s, j0);
@@ -43,7 +43,7 @@ __device__ __forceinline__ void apply_rest(const void* __restrict__ u, const voi
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             const Tile t = walk_tile(g, s, wl, min(j + q, s.count - 1));
-            const uint32_t off = tile_access(t, lane).off;
+            const uint32_t off = tile_access<kRowHeads<DT, VEC>>(t, lane).off;
             ru[q] = tile_load<DT, VEC, kStream>(u, t, off);
             if constexpr (BM == kBwdFromXZ) rz[q] = tile_load<DT, VEC, kStream>(zs, t, off);
             rg[q] = tile_load<DT, VEC, kStream>(dzdx, t, off);
@@ -54,7 +54,7 @@ __device__ __forceinline__ void apply_rest(const void* __restrict__ u, const voi
         for (int q = 0; q < kRestU; ++q) {
             if (j + q < s.count) {
                 const Tile t = walk_tile(g, s, w, j + q);
-                const TileAccess a = tile_access(t, lane);
+                const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
                 if (a.live) {
                     float tu[VEC], tz[VEC], tg[VEC];
                     unpack<DT, VEC>(ru[q], tu);
@@ -91,8 +91,8 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
     __shared__ uint32_t stage[4 * kMaxSlicesOnChip];
     const SliceId id = slice_id(g);
     const uint64_t chan = id.c * g.row_bytes;
-    const SliceTiles s = slice_tiles(g, id.p);
-    const uint32_t lane = tile_lane<AB>(g);
+    const SliceTiles s = slice_tiles(g, id.p, dzdx);
+    const TileLane lane = tile_lane<AB>(g);
 
     const SliceSync sync = slice_sync(sa, g, id.c);
     const uint64_t seen = g.P > 1 && threadIdx.x == 0 ? agent_load(sync.done) : 0;
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const Tile t = walk_tile(g, s, w, s.count ? min(uint32_t(j), s.count - 1) : 0);
-            const uint32_t off = tile_access(t, lane).off;
+            const uint32_t off = tile_access<kRowHeads<DT, VEC>>(t, lane).off;
             ku[j] = tile_load<DT, VEC, kStream>(zs, t, off);
             kg[j] = tile_load<DT, VEC, kStream>(dzdx, t, off);
             if (j + 1 < s.count) walk_next(g, w);
@@ -129,26 +129,26 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const Tile t = walk_tile(g, s, w, s.count ? min(uint32_t(j), s.count - 1) : 0);
-            ku[j] = tile_load<DT, VEC, kStream>(u, t, tile_access(t, lane).off);
+            ku[j] = tile_load<DT, VEC, kStream>(u, t, tile_access<kRowHeads<DT, VEC>>(t, lane).off);
             if (j + 1 < s.count) walk_next(g, w);
         }
     } else {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const Tile t = walk_tile(g, s, w, s.count ? min(uint32_t(j), s.count - 1) : 0);
-            const uint32_t off = tile_access(t, lane).off;
+            const uint32_t off = tile_access<kRowHeads<DT, VEC>>(t, lane).off;
             ku[j] = tile_load<DT, VEC, kStream>(u, t, off);
             kg[j] = tile_load<DT, VEC, kStream>(dzdx, t, off);
             if (j + 1 < s.count) walk_next(g, w);
         }
     }
-    typename Elem<DT>::T tail_u[kTails], tail_z[kTails], tail_g[kTails];
+    typename Elem<DT>::T edge_u[kEdges], edge_z[kEdges], edge_g[kEdges];
 #pragma unroll
-    for (int i = 0; i < kTails; ++i) {
-        const Tail t = tail_pos<EB>(g, chan, id.p, i);
-        tail_u[i] = tail_load<DT>(u, t);
-        if constexpr (XZ) tail_z[i] = tail_load<DT>(zs, t);
-        tail_g[i] = tail_load<DT>(dzdx, t);
+    for (int i = 0; i < kEdges; ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, id.p, i);
+        edge_u[i] = edge_load<DT>(u, t);
+        if constexpr (XZ) edge_z[i] = edge_load<DT>(zs, t);
+        edge_g[i] = edge_load<DT>(dzdx, t);
     }
     sched_fence();
     const float gamma_c = prm.gamma[id.c], beta_c = prm.beta[id.c];
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         if (j < sb.count) {
-            const TileAccess a = tile_access(walk_tile(g, sb, wa, j), lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j), lane);
             if (a.live)
                 accumulate(ku[j], kg[j], [&](int e) {
                     return ((negm[(j * VEC + e) / 32 % NW] >> ((j * VEC + e) % 32)) & 1u) != 0;
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             const Tile t = walk_tile(g, sb, w, min(j + q, sb.count - 1));
-            const uint32_t off = tile_access(t, lane).off;
+            const uint32_t off = tile_access<kRowHeads<DT, VEC>>(t, lane).off;
             if (S > 0 && j + q < R + S) {
                 ru[q] = tile_load<DT, VEC, kStream>(u, t, off);
                 if constexpr (XZ) rz[q] = tile_load<DT, VEC, kStream>(zs, t, off);
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             if (j + q < sb.count) {
-                const TileAccess a = tile_access(walk_tile(g, sb, wa, j + q), lane);
+                const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j + q), lane);
                 uint32_t bits = 0;
                 if constexpr (XZ) {
                     float tz[VEC];
@@ -236,27 +236,27 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
         }
     }
 
-    float tu2[kTails], tz2[kTails], tg2[kTails];
+    float tu2[kEdges], tz2[kEdges], tg2[kEdges];
 #pragma unroll
-    for (int i = 0; i < kTails; ++i) {
-        tu2[i] = static_cast<float>(tail_u[i]);
-        tz2[i] = XZ ? static_cast<float>(tail_z[i]) : 0.f;
-        tg2[i] = static_cast<float>(tail_g[i]);
+    for (int i = 0; i < kEdges; ++i) {
+        tu2[i] = static_cast<float>(edge_u[i]);
+        tz2[i] = XZ ? static_cast<float>(edge_z[i]) : 0.f;
+        tg2[i] = static_cast<float>(edge_g[i]);
     }
-    for (uint32_t i = 0; i < tail_rounds(g); ++i) {
-        const Tail t = tail_pos<EB>(g, chan, id.p, i);
+    for (uint32_t i = 0; i < edge_rounds(g); ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, id.p, i);
         if (!t.live) continue;
         float dy, w1;
-        if (i < kTails)
+        if (i < kEdges)
             el(i == 0 ? tu2[0] : tu2[1], i == 0 ? tz2[0] : tz2[1], i == 0 ? tg2[0] : tg2[1], dy, w1);
         else
-            el(static_cast<float>(tail_load<DT>(u, t)),
-               XZ ? static_cast<float>(tail_load<DT>(zs, t)) : 0.f,
-               static_cast<float>(tail_load<DT>(dzdx, t)), dy, w1);
+            el(static_cast<float>(edge_load<DT>(u, t)),
+               XZ ? static_cast<float>(edge_load<DT>(zs, t)) : 0.f,
+               static_cast<float>(edge_load<DT>(dzdx, t)), dy, w1);
         acc_dy += dy;
         acc_dyw += dy * w1;
     }
-    static_assert(kTails == 2, "the tail elements kept in registers");
+    static_assert(kEdges == 2, "the edge elements kept in registers");
 
     // The block's sums: wave partials in LDS, combined by every wave in the
     // same order.
@@ -333,11 +333,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
         }
         tile_store<DT, VEC>(dzdx, t, off, tg);
     };
-    if (g.tails) {
+    if (g.edges) {
 #pragma unroll
-        for (int i = 0; i < kTails; ++i) {
-            const Tail t = tail_pos<EB>(g, chan, id.p, i);
-            if (t.live) tail_store<DT>(dzdx, t, dx_of(tu2[i], tz2[i], tg2[i]));
+        for (int i = 0; i < kEdges; ++i) {
+            const Edge t = edge_pos<EB>(g, chan, s, id.p, i);
+            if (t.live) edge_store<DT>(dzdx, t, dx_of(tu2[i], tz2[i], tg2[i]));
         }
     }
     const SliceTiles sc = slice_again(s);
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
     for (int j = 0; j < R; ++j) {
         if (j < sc.count) {
             const Tile t = walk_tile(g, sc, w, j);
-            const TileAccess a = tile_access(t, lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
             if (a.live)
                 emit(t, a.off, ku[j], kg[j], [&](int e) {
                     return ((negm[(j * VEC + e) / 32 % NW] >> ((j * VEC + e) % 32)) & 1u) != 0;
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
 #pragma unroll 1
         for (uint32_t j = R; j < min(sc.count, uint32_t(R + S)); ++j) {
             const Tile t = walk_tile(g, sc, w, j);
-            const TileAccess a = tile_access(t, lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
             const uint32_t bits = XZ ? ls[XZ ? j - R : 0][threadIdx.x] : 0u;
             if (a.live)
                 emit(t, a.off, lu[j - R][threadIdx.x], lg[j - R][threadIdx.x],
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
             walk_next(g, w);
         }
     }
-    apply_rest<DT, VEC, BM>(u, zs, dzdx, g, chan, sc, lane, R + S, id.p, kTails, dx_of);
+    apply_rest<DT, VEC, BM>(u, zs, dzdx, g, chan, sc, lane, R + S, id.p, kEdges, dx_of);
     if (g.P == 1) return;
     lds_barrier();
     if (rest_s) {
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
         slice_abandoned(sync, id.p, left);
         for (uint32_t q = 0; q < g.P; ++q)
             if (left[q])
-                apply_rest<DT, VEC, BM>(u, zs, dzdx, g, chan, slice_tiles(g, q), lane, 0, q, 0,
+                apply_rest<DT, VEC, BM>(u, zs, dzdx, g, chan, slice_tiles(g, q, dzdx), lane, 0, q, 0,
                                         dx_of);
     }
 }

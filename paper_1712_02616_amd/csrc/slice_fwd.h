@@ -9,10 +9,10 @@
 // Measured (forward us, before: two streaming passes, or narrow accesses):
 // (32, 64, 112x112) fp16 29.3 -> 23.7, (8, 64, 256x256) 35.6 -> 27.6 (2 b per
 // element at 4.9 TB/s), (8, 20, 224x224) bf16 16.9 -> 13.3, (8, 256, 129x129)
-// fp16 115 -> 35.5, (2, 16, 8x8) fp32 4.9 -> 3.9.  With the exchange left out
+// fp16 115 -> 32.6, (8, 512, 65x65) 28.3 -> 16.7, (2, 16, 8x8) fp32 4.9 -> 3.9.  With the exchange left out
 // (a timing copy) the first two take 3 us less.  The code of a phase must
-// stay short: with the tails of ragged rows in the unrolled loops the kernel
-// was 14000 instructions, and fetching them cost 4 us a call.
+// stay short: with ragged rows' left-over elements in the unrolled loops the
+// kernel was 14000 instructions, and fetching them cost 4 us a call.
 
 #pragma once
 
@@ -54,27 +54,27 @@ __device__ __forceinline__ void emit(void* __restrict__ xz, const Tile& t, uint3
 }
 
 template <int DT, int FM, bool SMALL_SLOPE>
-__device__ __forceinline__ void emit_tail(void* __restrict__ xz, const Tail& t, float x,
+__device__ __forceinline__ void emit_edge(void* __restrict__ xz, const Edge& t, float x,
                                           const ApplyK& k) {
     float z;
     const float v = out_of<DT, FM, SMALL_SLOPE>(x, k, z);
-    tail_store<DT>(FM == kFwdOut ? k.out : xz, t, v);
-    if constexpr (FM == kFwdCkpt) tail_store<DT>(k.out, t, z);
+    edge_store<DT>(FM == kFwdOut ? k.out : xz, t, v);
+    if constexpr (FM == kFwdCkpt) edge_store<DT>(k.out, t, z);
 }
 
-// Outputs of the slice's accesses from j0 on and tail elements from i0 on,
+// Outputs of the slice's accesses from j0 on and edge elements from i0 on,
 // read from memory.
 constexpr int kRestU = 4;  // accesses in flight per thread past the resident ones
 
 template <int DT, int VEC, int FM, bool SMALL_SLOPE>
 __device__ __forceinline__ void apply_rest(void* __restrict__ xz, const TileGeom& g, uint64_t chan,
-                                           const SliceTiles& s, uint32_t lane, uint32_t j0,
+                                           const SliceTiles& s, const TileLane& lane, uint32_t j0,
                                            uint32_t p, uint32_t i0, const ApplyK& k) {
     constexpr int EB = static_cast<int>(sizeof(typename Elem<DT>::T));
-    for (uint32_t i = i0; i < tail_rounds(g); ++i) {
-        const Tail t = tail_pos<EB>(g, chan, p, i);
+    for (uint32_t i = i0; i < edge_rounds(g); ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, p, i);
         if (t.live)
-            emit_tail<DT, FM, SMALL_SLOPE>(xz, t, static_cast<float>(tail_load<DT>(xz, t)), k);
+            emit_edge<DT, FM, SMALL_SLOPE>(xz, t, static_cast<float>(edge_load<DT>(xz, t)), k);
     }
     if (j0 >= s.count) return;
     TileWalk w = walk_begin(g, chan, s, j0);
@@ -84,7 +84,7 @@ __device__ __forceinline__ void apply_rest(void* __restrict__ xz, const TileGeom
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             const Tile t = walk_tile(g, s, wl, min(j + q, s.count - 1));
-            r[q] = tile_load<DT, VEC, kStream>(xz, t, tile_access(t, lane).off);
+            r[q] = tile_load<DT, VEC, kStream>(xz, t, tile_access<kRowHeads<DT, VEC>>(t, lane).off);
             if (j + q + 1 < s.count) walk_next(g, wl);
         }
         sched_fence();
@@ -92,7 +92,7 @@ __device__ __forceinline__ void apply_rest(void* __restrict__ xz, const TileGeom
         for (int q = 0; q < kRestU; ++q) {
             if (j + q < s.count) {
                 const Tile t = walk_tile(g, s, w, j + q);
-                const TileAccess a = tile_access(t, lane);
+                const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
                 if (a.live) emit<DT, VEC, FM, SMALL_SLOPE>(xz, t, a.off, r[q], k);
             }
             walk_next(g, w);
@@ -103,17 +103,17 @@ __device__ __forceinline__ void apply_rest(void* __restrict__ xz, const TileGeom
 
 template <int DT, int VEC, int R, int S, int FM, bool SMALL_SLOPE>
 __device__ __forceinline__ void apply_all(void* __restrict__ xz, const TileGeom& g, uint64_t chan,
-                                          const SliceTiles& s, uint32_t lane,
+                                          const SliceTiles& s, const TileLane& lane,
                                           const raw_t<DT, VEC> (&keep)[R],
                                           const raw_t<DT, VEC> (&lx)[S > 0 ? S : 1][kThreads],
-                                          const float (&tails)[kTails], uint32_t p,
+                                          const float (&edges)[kEdges], uint32_t p,
                                           const ApplyK& k) {
     constexpr int EB = static_cast<int>(sizeof(typename Elem<DT>::T));
-    if (g.tails) {
+    if (g.edges) {
 #pragma unroll
-        for (int i = 0; i < kTails; ++i) {
-            const Tail t = tail_pos<EB>(g, chan, p, i);
-            if (t.live) emit_tail<DT, FM, SMALL_SLOPE>(xz, t, tails[i], k);
+        for (int i = 0; i < kEdges; ++i) {
+            const Edge t = edge_pos<EB>(g, chan, s, p, i);
+            if (t.live) emit_edge<DT, FM, SMALL_SLOPE>(xz, t, edges[i], k);
         }
     }
     TileWalk w = walk_begin(g, chan, s);
@@ -121,7 +121,7 @@ __device__ __forceinline__ void apply_all(void* __restrict__ xz, const TileGeom&
     for (int j = 0; j < R; ++j) {
         if (j < s.count) {
             const Tile t = walk_tile(g, s, w, j);
-            const TileAccess a = tile_access(t, lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
             if (a.live) emit<DT, VEC, FM, SMALL_SLOPE>(xz, t, a.off, keep[j], k);
         }
         walk_next(g, w);
@@ -131,12 +131,12 @@ __device__ __forceinline__ void apply_all(void* __restrict__ xz, const TileGeom&
 #pragma unroll 1
         for (uint32_t j = R; j < min(s.count, uint32_t(R + S)); ++j) {
             const Tile t = walk_tile(g, s, w, j);
-            const TileAccess a = tile_access(t, lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(t, lane);
             if (a.live) emit<DT, VEC, FM, SMALL_SLOPE>(xz, t, a.off, lx[j - R][threadIdx.x], k);
             walk_next(g, w);
         }
     }
-    apply_rest<DT, VEC, FM, SMALL_SLOPE>(xz, g, chan, s, lane, R + S, p, kTails, k);
+    apply_rest<DT, VEC, FM, SMALL_SLOPE>(xz, g, chan, s, lane, R + S, p, kEdges, k);
 }
 
 // Bound by HBM bandwidth: 2 b per element (checkpointing 3 b) plus the
@@ -154,8 +154,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
     __shared__ uint32_t stage[6 * kMaxSlicesOnChip];
     const SliceId id = slice_id(g);
     const uint64_t chan = id.c * g.row_bytes;
-    const SliceTiles s = slice_tiles(g, id.p);
-    const uint32_t lane = tile_lane<AB>(g);
+    const SliceTiles s = slice_tiles(g, id.p, xz);
+    const TileLane lane = tile_lane<AB>(g);
 
     const SliceSync sync = slice_sync(sa, g, id.c);
     const uint64_t seen = g.P > 1 && threadIdx.x == 0 ? agent_load(sync.done) : 0;
@@ -166,12 +166,12 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const Tile t = walk_tile(g, s, w, s.count ? min(uint32_t(j), s.count - 1) : 0);
-        keep[j] = tile_load<DT, VEC, kStream>(xz, t, tile_access(t, lane).off);
+        keep[j] = tile_load<DT, VEC, kStream>(xz, t, tile_access<kRowHeads<DT, VEC>>(t, lane).off);
         if (j + 1 < s.count) walk_next(g, w);
     }
-    typename Elem<DT>::T tail_raw[kTails];
+    typename Elem<DT>::T edge_raw[kEdges];
 #pragma unroll
-    for (int i = 0; i < kTails; ++i) tail_raw[i] = tail_load<DT>(xz, tail_pos<EB>(g, chan, id.p, i));
+    for (int i = 0; i < kEdges; ++i) edge_raw[i] = edge_load<DT>(xz, edge_pos<EB>(g, chan, s, id.p, i));
     sched_fence();
     const float gamma_c = prm.gamma[id.c], beta_c = prm.beta[id.c];
     const float rm_c = prm.running_mean[id.c], rv_c = prm.running_var[id.c];
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         if (j < sb.count) {
-            const TileAccess a = tile_access(walk_tile(g, sb, wa, j), lane);
+            const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j), lane);
             if (a.live) accumulate(keep[j]);
         }
         walk_next(g, wa);
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             const Tile t = walk_tile(g, sb, w, min(j + q, sb.count - 1));
-            const uint32_t off = tile_access(t, lane).off;
+            const uint32_t off = tile_access<kRowHeads<DT, VEC>>(t, lane).off;
             r[q] = S > 0 && j + q < R + S ? tile_load<DT, VEC, kStream>(xz, t, off)
                                           : tile_load<DT, VEC, kCached>(xz, t, off);
             if (j + q + 1 < sb.count) walk_next(g, w);
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 #pragma unroll
         for (int q = 0; q < kRestU; ++q) {
             if (j + q < sb.count) {
-                const TileAccess a = tile_access(walk_tile(g, sb, wa, j + q), lane);
+                const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j + q), lane);
                 if (S > 0 && j + q < R + S) lx[j + q - R][threadIdx.x] = r[q];
                 if (a.live) accumulate(r[q]);
             }
@@ -236,14 +236,16 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
         }
     }
 
-    float tails[kTails];
+    float edges[kEdges];
 #pragma unroll
-    for (int i = 0; i < kTails; ++i) tails[i] = static_cast<float>(tail_raw[i]);
-    for (uint32_t i = 0; i < tail_rounds(g); ++i) {
-        const Tail t = tail_pos<EB>(g, chan, id.p, i);
-        if (t.live) add(i == 0 ? tails[0] : i == 1 ? tails[1] : static_cast<float>(tail_load<DT>(xz, t)));
+    for (int i = 0; i < kEdges; ++i) edges[i] = static_cast<float>(edge_raw[i]);
+    for (uint32_t i = 0; i < edge_rounds(g); ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, id.p, i);
+        if (t.live) add(i == 0   ? edges[0]
+                        : i == 1 ? edges[1]
+                                 : static_cast<float>(edge_load<DT>(xz, t)));
     }
-    static_assert(kTails == 2, "the tail elements kept in registers");
+    static_assert(kEdges == 2, "the edge elements kept in registers");
 
     // The block's sums about one shift, in double: wave partials in LDS,
     // combined by every wave in the same order.
@@ -344,9 +346,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
     if (last && threadIdx.x == 0) statistics();
     const bool small_slope = prm.slope <= 1.f;
     if (small_slope)
-        apply_all<DT, VEC, R, S, FM, true>(xz, g, chan, slice_again(s), lane, keep, lx, tails, id.p, k);
+        apply_all<DT, VEC, R, S, FM, true>(xz, g, chan, slice_again(s), lane, keep, lx, edges, id.p, k);
     else
-        apply_all<DT, VEC, R, S, FM, false>(xz, g, chan, slice_again(s), lane, keep, lx, tails, id.p, k);
+        apply_all<DT, VEC, R, S, FM, false>(xz, g, chan, slice_again(s), lane, keep, lx, edges, id.p, k);
     if (g.P == 1) return;
     lds_barrier();
     if (rest_s) {
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
         slice_abandoned(sync, id.p, left);
         for (uint32_t q = 0; q < g.P; ++q) {
             if (!left[q]) continue;
-            const SliceTiles sq = slice_tiles(g, q);
+            const SliceTiles sq = slice_tiles(g, q, xz);
             if (small_slope)
                 apply_rest<DT, VEC, FM, true>(xz, g, chan, sq, lane, 0, q, 0, k);
             else

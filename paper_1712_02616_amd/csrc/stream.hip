@@ -286,14 +286,14 @@ __global__ __launch_bounds__(kThreads) void recompute_kernel(const void* __restr
 // 25.6 us, 5.2 TB/s.
 constexpr int kPointU = 4;
 
-template <int DT, int VEC, bool RECOMPUTE>
+template <int DT, int VEC, bool RECOMPUTE, bool HEADS>
 __global__ __launch_bounds__(kThreads) void pointwise_kernel(const void* src, void* dst, TileGeom g,
                                                              FwdParams prm) {
     constexpr int AB = RawAccess<DT, VEC>::kBytes, EB = AB / VEC;
     const SliceId id = slice_id(g);
     const uint64_t chan = id.c * g.row_bytes;
-    const SliceTiles s = slice_tiles(g, id.p);
-    const uint32_t lane = tile_lane<AB>(g);
+    const SliceTiles s = slice_tiles(g, id.p, dst);
+    const TileLane lane = tile_lane<AB>(g);
     const float gamma = prm.gamma[id.c], beta = prm.beta[id.c], slope = prm.slope;
     float mean_hi = 0.f, scale = gamma;
     if constexpr (!RECOMPUTE) {
@@ -305,10 +305,10 @@ __global__ __launch_bounds__(kThreads) void pointwise_kernel(const void* src, vo
         const float y = fmaf(x - mean_hi, scale, beta);
         return y >= 0.f ? y : slope * y;
     };
-    for (uint32_t i = 0; i < tail_rounds(g); ++i) {
-        const Tail t = tail_pos<EB>(g, chan, id.p, i);
-        if (t.live) tail_store<DT>(dst, t, out(static_cast<float>(tail_load<DT>(src, t))));
-    }
+    // The edges' loads go out first and wait until the tiles are done.
+    typename Elem<DT>::T edge[kEdges];
+#pragma unroll
+    for (int i = 0; i < kEdges; ++i) edge[i] = edge_load<DT>(src, edge_pos<EB>(g, chan, s, id.p, i));
     TileWalk w = walk_begin(g, chan, s);
     for (uint32_t j = 0; j < s.count; j += kPointU) {
         raw_t<DT, VEC> r[kPointU];
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void pointwise_kernel(const void* src, vo
 #pragma unroll
         for (int q = 0; q < kPointU; ++q) {
             t[q] = walk_tile(g, s, w, min(j + q, s.count - 1));
-            a[q] = tile_access(t[q], lane);
+            a[q] = tile_access<HEADS>(t[q], lane);
             r[q] = tile_load<DT, VEC, kStream>(src, t[q], a[q].off);
             if (j + q + 1 < s.count) walk_next(g, w);
         }
@@ -333,6 +333,14 @@ __global__ __launch_bounds__(kThreads) void pointwise_kernel(const void* src, vo
             }
         }
     }
+    for (uint32_t i = 0; i < edge_rounds(g); ++i) {
+        const Edge t = edge_pos<EB>(g, chan, s, id.p, i);
+        if (t.live)
+            edge_store<DT>(dst, t, out(static_cast<float>(i == 0   ? edge[0]
+                                                          : i == 1 ? edge[1]
+                                                                   : edge_load<DT>(src, t))));
+    }
+    static_assert(kEdges == 2, "the edge elements kept in registers");
 }
 
 // One batch of the backward's tensors at accesses idx(0..U-1), raw: u, the
@@ -678,10 +686,16 @@ void go_pointwise(const void* src, void* dst, const TileGeom& g, const FwdParams
                   bool recompute, hipStream_t st) {
     constexpr int V = 16 / static_cast<int>(sizeof(typename Elem<DT>::T));
     const dim3 grid(g.C * g.P);
-    if (recompute)
-        pointwise_kernel<DT, V, true><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
-    else
-        pointwise_kernel<DT, V, false><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
+    if (kRowHeads<DT, V> && g.head_mask) {
+        if (recompute)
+            pointwise_kernel<DT, V, true, kRowHeads<DT, V>><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
+        else
+            pointwise_kernel<DT, V, false, kRowHeads<DT, V>><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
+    } else if (recompute) {
+        pointwise_kernel<DT, V, true, false><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
+    } else {
+        pointwise_kernel<DT, V, false, false><<<grid, kThreads, 0, st>>>(src, dst, g, prm);
+    }
 }
 
 }  // namespace

@@ -10,13 +10,16 @@
 // (A division by the row length and 64-bit vector arithmetic per access, as
 // the general mapping does, costs a short channel 7-12% of its time.)
 //
-// Ragged rows.  Rows whose length no 8-byte access divides still move in
-// 16-byte accesses, at the alignment of an element, and the up to seven
-// elements at a row's end that do not fill one (its tail) move one by one:
-// the tails of a channel are numbered through and dealt out to the threads.
-// (Unaligned 16-byte accesses stream at the aligned rate, measured 5.6 TB/s
-// read and write against 5.4-5.7; 2-byte accesses need eight times the
-// instructions.)
+// Ragged rows.  Rows that 16-byte accesses do not divide still move in them,
+// as many to each row, and the elements left over at a row's two ends (its
+// edges) move one by one: the edges of a channel are numbered through and
+// dealt out to the threads.  The accesses of a long row start at the first
+// 16-byte boundary in it, so that up to 15 bytes (its head) come before them;
+// those of a short row start at the row, at the alignment of an element, which
+// leaves fewer elements over.  (Unaligned accesses are allowed but cost where
+// they are aligned to 2 bytes only: forward / backward of (8, 512, 65x65) fp16
+// 20.9 / 30.3 us with them, 16.7 / 23.2 with heads; 2-byte accesses 28.3 /
+// 38.0.)
 #pragma once
 
 #include "fused.h"
@@ -30,7 +33,7 @@ struct TileGeom {
     uint32_t split_rows;  // 1: a row holds `per` tiles; 0: a tile holds `per` rows
     uint32_t per;
     iabn_divmagic_t per_div;  // division by per
-    uint32_t vrow;            // whole accesses per row
+    uint32_t vrow;            // accesses per row
     iabn_divmagic_t vrow_div;
     uint32_t cap;         // byte offset of a tile's last access (split_rows: in the row)
     uint32_t cap_end;     // the same for a channel's last tile, which may hold fewer rows
@@ -41,42 +44,59 @@ struct TileGeom {
     uint64_t step_base;   // TileWalk::base
     uint64_t row_bytes;
     uint64_t nstride;     // bytes between rows of a channel
-    uint32_t tail;        // elements at a row's end that no access holds
-    iabn_divmagic_t tail_div;
-    uint32_t tails;       // of a channel: N * tail
-    uint32_t tail_at;     // byte offset in a row of its tail
+    uint32_t head_mask;   // 15: a row's accesses start at its first 16-byte boundary; 0: at the row
+    uint32_t edge;        // elements of a row that no access holds
+    iabn_divmagic_t edge_div;
+    uint32_t edges;       // of a channel: N * edge
+    uint32_t body_bytes;  // of a row's accesses
     uint32_t xcd_order;   // slices in contiguous ranges per XCD (see block_slice)
     uint32_t P;           // slices (blocks) per channel
     double m, inv_m;      // elements per channel
 };
 
-// A lane's byte offset in a tile (split_rows: from the tile's start, else
-// from its first row; a lane with no place in it is past Tile::cap).
+// A lane's place in every tile: its byte offset (split_rows: from the tile's
+// start, else from its first row; a lane with no place in it is past
+// Tile::cap), and that of its row, for the row's head.
+struct TileLane {
+    uint32_t off, row;
+};
+
 template <int AB>
-__device__ __forceinline__ uint32_t tile_lane(const TileGeom& g) {
+__device__ __forceinline__ TileLane tile_lane(const TileGeom& g) {
     const uint32_t tl = threadIdx.x & (g.lanes - 1);
-    if (g.split_rows) return tl * AB;
+    if (g.split_rows) return {tl * AB, 0u};
     const uint32_t r = iabn_divmagic_div(tl, g.vrow_div);
-    return r * static_cast<uint32_t>(g.nstride) + (tl - r * g.vrow) * AB;
+    const uint32_t row = r * static_cast<uint32_t>(g.nstride);
+    return {row + (tl - r * g.vrow) * AB, row};
 }
 
 // The uniform part of a tile: lane offset + add is the lane's access, at
-// `base`, if it is at most `cap`.
+// `base` and its row's head, if it is at most `cap`.
 struct Tile {
     uint64_t base;
     uint32_t add, cap;
+    uint32_t head, head_mask;  // bytes to the first boundary after base, unmasked
 };
 
 // A lane's access in a tile: lanes without one get the tile's last access
-// (a line the tile reads anyway).
+// (a line the tile reads anyway; with any head it lies in its row, whose
+// edges are as long as the longest head).
 struct TileAccess {
     uint32_t off;
     bool live;
 };
 
-__device__ __forceinline__ TileAccess tile_access(const Tile& t, uint32_t lane) {
-    const uint32_t u = lane + t.add;
-    return {min(u, t.cap), u <= t.cap};
+// Only rows aligned to no more than 2 bytes have heads.
+template <int DT, int VEC>
+constexpr bool kRowHeads = sizeof(typename Elem<DT>::T) == 2 && VEC == 8;
+
+// (Compiled in for fp32 too, unused, they made its inference forward 18%
+// slower.)
+template <bool HEADS>
+__device__ __forceinline__ TileAccess tile_access(const Tile& t, const TileLane& lane) {
+    const uint32_t u = lane.off + t.add;
+    const uint32_t head = HEADS ? (t.head - lane.row) & t.head_mask : 0u;
+    return {min(u, t.cap) + head, u <= t.cap};
 }
 
 // An access of 16 bytes needs only the alignment of an element; narrower
@@ -128,15 +148,18 @@ struct SliceTiles {
     uint32_t first, count;  // uniform per wave
     uint32_t end;           // j of the channel's last tile, if the slice has it (a slice
                             // without tiles loads tile 0, as j = 0)
+    uint32_t origin;        // low bits of the address of the tensor the rows are aligned in
 };
 
-__device__ __forceinline__ SliceTiles slice_tiles(const TileGeom& g, uint32_t p) {
+__device__ __forceinline__ SliceTiles slice_tiles(const TileGeom& g, uint32_t p,
+                                                  const void* tensor) {
     const uint32_t groups = kThreads / g.lanes;
     const uint32_t sub = __builtin_amdgcn_readfirstlane(threadIdx.x / g.lanes);
     SliceTiles s;
     s.first = p * groups + sub;
     s.count = s.first < g.tiles ? (g.tiles - s.first + g.step - 1) / g.step : 0;
     const bool ends = s.count ? s.first + (s.count - 1) * g.step == g.tiles - 1 : g.tiles == 1;
+    s.origin = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(tensor));
     s.end = ends ? (s.count ? s.count - 1 : 0) : ~0u;
     return s;
 }
@@ -182,41 +205,47 @@ __device__ __forceinline__ void walk_next(const TileGeom& g, TileWalk& w) {
 // The slice's j-th tile, where the walk is.
 __device__ __forceinline__ Tile walk_tile(const TileGeom& g, const SliceTiles& s, const TileWalk& w,
                                           uint32_t j) {
-    return {w.base, w.at, j == s.end ? g.cap_end : g.cap};
+    return {w.base, w.at, j == s.end ? g.cap_end : g.cap,
+            0u - (s.origin + static_cast<uint32_t>(w.base)), g.head_mask};
 }
 
-// Tails: element i of a thread of slice p (i = 0, 1, ...: elements (i*P + p)
+// Edges: element i of a thread of slice p (i = 0, 1, ...: elements (i*P + p)
 // * 256 + thread of the channel's), or one that is not live, at the
 // channel's first element.
-struct Tail {
+struct Edge {
     uint64_t at;
     bool live;
 };
 
 template <int EB>
-__device__ __forceinline__ Tail tail_pos(const TileGeom& g, uint64_t chan, uint32_t p, uint32_t i) {
+__device__ __forceinline__ Edge edge_pos(const TileGeom& g, uint64_t chan, const SliceTiles& s,
+                                         uint32_t p, uint32_t i) {
     const uint32_t e = (i * g.P + p) * kThreads + threadIdx.x;
-    const uint32_t row = iabn_divmagic_div(e, g.tail_div);
-    Tail t;
-    t.live = e < g.tails;
-    t.at = t.live ? chan + row * g.nstride + g.tail_at + (e - row * g.tail) * EB : chan;
+    const uint32_t row = iabn_divmagic_div(e, g.edge_div);
+    const uint64_t start = chan + row * g.nstride;
+    const uint32_t head = (0u - (s.origin + static_cast<uint32_t>(start))) & g.head_mask;
+    uint32_t at = (e - row * g.edge) * EB;
+    if (at >= head) at += g.body_bytes;
+    Edge t;
+    t.live = e < g.edges;
+    t.at = t.live ? start + at : chan;
     return t;
 }
 
-// Tail elements a thread keeps in registers; it reads the rest again.
-constexpr int kTails = 2;
+// Edge elements a thread keeps in registers; it reads the rest again.
+constexpr int kEdges = 2;
 
-__device__ __forceinline__ uint32_t tail_rounds(const TileGeom& g) {
-    return (g.tails + g.P * kThreads - 1) / (g.P * kThreads);
+__device__ __forceinline__ uint32_t edge_rounds(const TileGeom& g) {
+    return (g.edges + g.P * kThreads - 1) / (g.P * kThreads);
 }
 
 template <int DT>
-__device__ __forceinline__ typename Elem<DT>::T tail_load(const void* base, const Tail& t) {
+__device__ __forceinline__ typename Elem<DT>::T edge_load(const void* base, const Edge& t) {
     using T = typename Elem<DT>::T;
     return *reinterpret_cast<const T*>(static_cast<const char*>(base) + t.at);
 }
 template <int DT>
-__device__ __forceinline__ void tail_store(void* base, const Tail& t, float v) {
+__device__ __forceinline__ void edge_store(void* base, const Edge& t, float v) {
     using T = typename Elem<DT>::T;
     *reinterpret_cast<T*>(static_cast<char*>(base) + t.at) = static_cast<T>(v);
 }
