@@ -507,13 +507,15 @@ int backward_impl(int bm, bool ii, const void* u, const void* zs, void* dz_dx, i
 // ---------------------------------------------------------------- static scratch
 
 // The scratch of iabn_forward_train_noalloc: the streaming kernels' partial
-// results, in a file-scope device array instead of a caller's workspace.
+// results and the slice-resident kernels' exchange, in a file-scope device
+// array instead of a caller's workspace.
 // Each device holds its own copy (zero-initialised when the library's code
 // object is loaded on it) until the process ends.  Its size bounds the
 // partials of one call: C * P slices * 4 waves * 32 bytes, at most 765
 // slices (C = 255, P = 3) where the forward takes the streaming kernels,
-// about 96 KiB.  Nothing in it needs to start at zero: every partial a call
-// reads was written by the same call.
+// about 96 KiB; at most kSliceBlocks slices of kSliceWords words, 64 KiB, where
+// it takes the slice-resident ones.  Nothing in it needs to start at zero:
+// every partial a call reads was written by the same call.
 constexpr size_t kScratchBytes = size_t(128) << 10;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

@@ -308,6 +308,11 @@ constexpr uint64_t kTagBits = 64 - kTagShift;
 #ifndef IABN_SLICE_POLLS
 #define IABN_SLICE_POLLS 256
 #endif
+// The channel's last block finds all sums in its first polls.  Only calls that
+// share a workspace at the same time, which the interface forbids, can have
+// overwritten them: its wait then ends too (in under a second), the results
+// being as undefined as such calls' always are.
+constexpr uint32_t kLastPolls = 1u << 20;
 
 struct SliceArgs {
     uint64_t* workspace;
@@ -321,7 +326,6 @@ struct SliceArgs {
 // polls it (with the counts beside the slots an exchange took 14 us).
 constexpr uint64_t kCountWords = 3;  // per slice: room between the counts
 constexpr uint64_t kSliceWords = kSlotWords + 1 + kCountWords;
-
 
 struct SliceSync {
     uint64_t* done;  // see slice_open
@@ -393,14 +397,13 @@ __device__ __forceinline__ void slice_publish(const SliceSync& s, uint32_t p,
 }
 
 // One wave: lane q < P gets slice q's pieces (through `stage`, block-shared).
-// Returns false if they have not all arrived in time (limit false: wait
-// without end, for sums that are known to be on their way).  Adjacent lanes
-// read adjacent words, so that a poll is a few requests: with a lane per
-// slot, the blocks of a channel kept its few lines so busy that an exchange
-// took 15 us.
+// Returns false if they have not all arrived after `limit` polls.  Adjacent
+// lanes read adjacent words, so that a poll is a few requests: with a lane
+// per slot, the blocks of a channel kept its few lines so busy that an
+// exchange took 15 us.
 template <int NP>
 __device__ __forceinline__ bool slice_collect(const SliceSync& s, uint32_t (&piece)[NP],
-                                              uint32_t* stage, bool limit) {
+                                              uint32_t* stage, uint32_t limit) {
     constexpr uint32_t kBatch = 4;
     const uint32_t words = 2 * NP * s.P;
     const uint32_t half = static_cast<uint32_t>((lane_id() & 1) ? s.key >> 32 : s.key);
@@ -420,7 +423,7 @@ __device__ __forceinline__ bool slice_collect(const SliceSync& s, uint32_t (&pie
                 if (at < words && (at & 1) == 0) stage[at / 2] = v;
             }
             if (__all(ok)) break;
-            if (limit && ++polls >= IABN_SLICE_POLLS) return false;
+            if (++polls >= limit) return false;
             __builtin_amdgcn_s_sleep(1);
         }
     }
@@ -439,7 +442,7 @@ template <int NP>
 __device__ __forceinline__ bool slice_wait(const SliceSync& s, uint32_t p, uint64_t seen,
                                            uint32_t (&piece)[NP], uint32_t* stage, uint64_t& done) {
     done = 0;
-    if (slice_collect(s, piece, stage, true)) return true;
+    if (slice_collect(s, piece, stage, IABN_SLICE_POLLS)) return true;
     if (lane_id() == 0) {
         agent_store(s.flag + p, s.tag);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -449,7 +452,7 @@ __device__ __forceinline__ bool slice_wait(const SliceSync& s, uint32_t p, uint6
     if (!__any(lane_id() == 0 && slice_last(s, done))) return false;
     // The last one has nobody to leave its slice to, and needs to wait for
     // nobody: every other block has published its sums.
-    return slice_collect(s, piece, stage, false);
+    return slice_collect(s, piece, stage, kLastPolls);
 }
 
 // The same wave, before it writes its part of the slice (a wait for the
