@@ -180,7 +180,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 
     // Shifted sums per thread (see fwd_stats_kernel); the shift is the first
     // value the thread loaded, an element of the channel even where the lane
-    // has no access in its first tile.
+    // has no access in its first tile.  fp32 within kRun elements, double
+    // across them: a thread holds several times the elements that narrow
+    // accesses give it in the channel-resident kernels, and one fp32 sum over
+    // all of them lost precision against those.
+    constexpr int kRun = 8;
+    constexpr int kRunAccesses = VEC < kRun ? kRun / VEC : 1;
+    double a1 = 0.0, a2 = 0.0;
     float shift, s1 = 0.f, s2 = 0.f;
     uint32_t n = 0;
     {
@@ -200,6 +206,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
 #pragma unroll
         for (int e = 0; e < VEC; ++e) add(t[e]);
     };
+    auto end_run = [&]() {
+        a1 += s1;
+        a2 += s2;
+        s1 = s2 = 0.f;
+    };
     const SliceTiles sb = slice_again(s);
     TileWalk wa = walk_begin(g, chan, sb);
 #pragma unroll
@@ -207,6 +218,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
         if (j < sb.count) {
             const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j), lane);
             if (a.live) accumulate(keep[j]);
+            if ((j + 1) % kRunAccesses == 0) end_run();
         }
         walk_next(g, wa);
         sched_fence();
@@ -231,9 +243,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
                 const TileAccess a = tile_access<kRowHeads<DT, VEC>>(walk_tile(g, sb, wa, j + q), lane);
                 if (S > 0 && j + q < R + S) lx[j + q - R][threadIdx.x] = r[q];
                 if (a.live) accumulate(r[q]);
+                if ((q + 1) % kRunAccesses == 0) end_run();
             }
             walk_next(g, wa);
         }
+        end_run();
     }
 
     float edges[kEdges];
@@ -244,13 +258,15 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_slice_kernel(void* __restrict
         if (t.live) add(i == 0   ? edges[0]
                         : i == 1 ? edges[1]
                                  : static_cast<float>(edge_load<DT>(xz, t)));
+        end_run();
     }
+    end_run();
     static_assert(kEdges == 2, "the edge elements kept in registers");
 
     // The block's sums about one shift, in double: wave partials in LDS,
     // combined by every wave in the same order.
     const double kw = __shfl(shift, 0, kWave);
-    double d1 = s1, d2 = s2, dn = n;
+    double d1 = a1, d2 = a2, dn = n;
     reshift(d1, d2, dn, shift, kw);
     d1 = wave_sum(d1);
     d2 = wave_sum(d2);
