@@ -415,10 +415,12 @@ __device__ __forceinline__ BwdApplyElem<BM> make_apply_elem(double A, double& sd
 }
 
 // 1/sqrt(v) in double: the hardware estimate refined by one Newton step
-// (relative error about 1e-14, far below the fp32 constants it feeds).
+// (relative error about 1e-14, far below the fp32 constants it feeds).  At
+// +inf and 0 the step is inf * 0; the estimate, 0 or inf, is the result.
 __device__ __forceinline__ double rsqrt_d(double v) {
     const double r = __builtin_amdgcn_rsq(v);
-    return r * (1.5 - 0.5 * v * r * r);
+    const double y = r * (1.5 - 0.5 * v * r * r);
+    return y == y ? y : r;
 }
 
 struct BwdParams {
