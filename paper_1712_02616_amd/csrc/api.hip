@@ -108,6 +108,7 @@ struct SlicePlan {
     TileGeom g;
     int vec;  // elements per access
     int R;    // accesses per thread the kernel holds
+    bool fine;  // backward: every element's terms to double (slice_bwd.h)
 };
 
 // Rows of at least a cache line that only 2- or 4-byte accesses divide (or
@@ -243,6 +244,7 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     out->g = slots64 < slots256 ? a : b;
     out->vec = v;
     TileGeom& g = out->g;
+    out->fine = ragged;
     const Split sp = split_channel(N * HW, C);
     const int64_t groups = kThreads / g.lanes;
     auto accesses = [&](int64_t P) { return (int64_t(g.tiles) + P * groups - 1) / (P * groups); };
@@ -487,7 +489,7 @@ int backward_impl(int bm, bool ii, const void* u, const void* zs, void* dz_dx, i
     SlicePlan sl;
     const Route route = plan_route(N, C, HW, dtype, g, true, bm == kBwdFromZ, &fp, &sl);
     if (route == Route::kSlice) {
-        if (!launch_bwd_slice(dtype, sl.vec, bm, u, zs, dz_dx, sl.g, sl.R,
+        if (!launch_bwd_slice(dtype, sl.vec, bm, sl.fine, u, zs, dz_dx, sl.g, sl.R,
                               slice_args(workspace), prm, st))
             return fail(IABN_ERR_HIP, "no sliced %s kernel built for R=%d", bwd_name(bm, ii), sl.R);
         return launched(bwd_name(bm, ii));

@@ -221,23 +221,23 @@ template <int DT>
 bool launch_fwd_slice_dt(int vec, int fm, void* xz, const TileGeom& g, int R, const SliceArgs& sa,
                          const FwdParams& prm, hipStream_t st);
 template <int DT>
-bool launch_bwd_slice_dt(int vec, int bm, const void* u, const void* zs, void* dzdx,
+bool launch_bwd_slice_dt(int vec, int bm, bool fine, const void* u, const void* zs, void* dzdx,
                          const TileGeom& g, int R, const SliceArgs& sa, const BwdParams& prm,
                          hipStream_t st);
 extern template bool launch_fwd_slice_dt<IABN_F32>(int, int, void*, const TileGeom&, int,
                                                  const SliceArgs&, const FwdParams&, hipStream_t);
-extern template bool launch_bwd_slice_dt<IABN_F32>(int, int, const void*, const void*, void*,
-                                                 const TileGeom&, int, const SliceArgs&,
+extern template bool launch_bwd_slice_dt<IABN_F32>(int, int, bool, const void*, const void*,
+                                                 void*, const TileGeom&, int, const SliceArgs&,
                                                  const BwdParams&, hipStream_t);
 extern template bool launch_fwd_slice_dt<IABN_F16>(int, int, void*, const TileGeom&, int,
                                                  const SliceArgs&, const FwdParams&, hipStream_t);
-extern template bool launch_bwd_slice_dt<IABN_F16>(int, int, const void*, const void*, void*,
-                                                 const TileGeom&, int, const SliceArgs&,
+extern template bool launch_bwd_slice_dt<IABN_F16>(int, int, bool, const void*, const void*,
+                                                 void*, const TileGeom&, int, const SliceArgs&,
                                                  const BwdParams&, hipStream_t);
 extern template bool launch_fwd_slice_dt<IABN_BF16>(int, int, void*, const TileGeom&, int,
                                                  const SliceArgs&, const FwdParams&, hipStream_t);
-extern template bool launch_bwd_slice_dt<IABN_BF16>(int, int, const void*, const void*, void*,
-                                                 const TileGeom&, int, const SliceArgs&,
+extern template bool launch_bwd_slice_dt<IABN_BF16>(int, int, bool, const void*, const void*,
+                                                 void*, const TileGeom&, int, const SliceArgs&,
                                                  const BwdParams&, hipStream_t);
 
 inline bool launch_fwd_slice(int dtype, int vec, int fm, void* xz, const TileGeom& g, int R,
@@ -247,12 +247,14 @@ inline bool launch_fwd_slice(int dtype, int vec, int fm, void* xz, const TileGeo
                                : launch_fwd_slice_dt<IABN_BF16>(vec, fm, xz, g, R, sa, prm, st);
 }
 
-inline bool launch_bwd_slice(int dtype, int vec, int bm, const void* u, const void* zs, void* dzdx,
-                             const TileGeom& g, int R, const SliceArgs& sa, const BwdParams& prm,
-                             hipStream_t st) {
-    return dtype == IABN_F32   ? launch_bwd_slice_dt<IABN_F32>(vec, bm, u, zs, dzdx, g, R, sa, prm, st)
-           : dtype == IABN_F16 ? launch_bwd_slice_dt<IABN_F16>(vec, bm, u, zs, dzdx, g, R, sa, prm, st)
-                               : launch_bwd_slice_dt<IABN_BF16>(vec, bm, u, zs, dzdx, g, R, sa, prm, st);
+inline bool launch_bwd_slice(int dtype, int vec, int bm, bool fine, const void* u, const void* zs,
+                             void* dzdx, const TileGeom& g, int R, const SliceArgs& sa,
+                             const BwdParams& prm, hipStream_t st) {
+    return dtype == IABN_F32
+               ? launch_bwd_slice_dt<IABN_F32>(vec, bm, fine, u, zs, dzdx, g, R, sa, prm, st)
+           : dtype == IABN_F16
+               ? launch_bwd_slice_dt<IABN_F16>(vec, bm, fine, u, zs, dzdx, g, R, sa, prm, st)
+               : launch_bwd_slice_dt<IABN_BF16>(vec, bm, fine, u, zs, dzdx, g, R, sa, prm, st);
 }
 
 // Accesses per thread (of each tensor) that the slice-resident kernels are

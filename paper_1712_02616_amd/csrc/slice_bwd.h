@@ -74,7 +74,7 @@ __device__ __forceinline__ void apply_rest(const void* __restrict__ u, const voi
 // Bound by HBM bandwidth: 3 b per element (standard block 4 b) plus the
 // exchange.  R = 24 accesses of each tensor and 8 more in LDS are what two
 // blocks per CU hold (two waves per SIMD, 256 registers; 64 KB of LDS each).
-template <int DT, int VEC, int R, int S, int BM>
+template <int DT, int VEC, int R, int S, int BM, bool FINE>
 __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __restrict__ u,
                                                                 const void* __restrict__ zs,
                                                                 void* __restrict__ dzdx, TileGeom g,
@@ -160,7 +160,13 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
     const BwdRecip rc = make_recip(gamma_c, prm.slope, g.inv_m);
     sched_fence();
 
-    // fp32 within one access, double across accesses (see bwd_fused_channel).
+    // fp32 within one access, double across accesses (see bwd_fused_channel);
+    // on ragged rows (FINE) every element's terms go to double, as the
+    // channel-resident kernels, which move such rows an element or two at a
+    // time, add up no more in fp32: the relative error of dbeta on (8, 512,
+    // 65x65) fp16 is 2.5e-8 (8 elements in fp32: 5.0e-8).  On all rows it
+    // would cost 2-3% ((32, 64, 112x112) fp16 32.3 -> 33.2 us; there 8
+    // elements are fewer than the streaming kernels add up).
     double acc_dy = 0.0, acc_dyw = 0.0;
     auto accumulate = [&](raw_t<DT, VEC> ru, raw_t<DT, VEC> rg, auto neg) {
         float tu[VEC], tg[VEC];
@@ -172,11 +178,18 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
             float dy, w;
             if constexpr (XZ) el.with_neg(neg(e), tu[e], tg[e], dy, w);
             else el(tu[e], 0.f, tg[e], dy, w);
-            sdy += dy;
-            sdyw = fmaf(dy, w, sdyw);
+            if constexpr (FINE) {
+                acc_dy += dy;
+                acc_dyw = fma(static_cast<double>(dy), static_cast<double>(w), acc_dyw);
+            } else {
+                sdy += dy;
+                sdyw = fmaf(dy, w, sdyw);
+            }
         }
-        acc_dy += sdy;
-        acc_dyw += sdyw;
+        if constexpr (!FINE) {
+            acc_dy += sdy;
+            acc_dyw += sdyw;
+        }
     };
     const SliceTiles sb = slice_again(s);
     TileWalk wa = walk_begin(g, chan, sb);
@@ -380,37 +393,38 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
     }
 }
 
-template <int DT, int V, int R, int S, int BM>
+template <int DT, int V, int R, int S, int BM, bool FINE>
 void go(const void* u, const void* zs, void* dzdx, const TileGeom& g, const SliceArgs& sa,
         const BwdParams& prm, hipStream_t st) {
-    bwd_slice_kernel<DT, V, R, S, BM>
+    bwd_slice_kernel<DT, V, R, S, BM, FINE>
         <<<dim3(g.C * g.P), kThreads, 0, st>>>(u, zs, dzdx, g, sa, prm);
 }
 
-template <int DT, int V, int BM>
+template <int DT, int V, int BM, bool FINE>
 bool launch_v(const void* u, const void* zs, void* dzdx, const TileGeom& g, int R,
               const SliceArgs& sa, const BwdParams& prm, hipStream_t st) {
-    if (R == 4) return go<DT, V, 4, 0, BM>(u, zs, dzdx, g, sa, prm, st), true;
-    if (R == 8) return go<DT, V, 8, 0, BM>(u, zs, dzdx, g, sa, prm, st), true;
-    if (R == 16) return go<DT, V, 16, 0, BM>(u, zs, dzdx, g, sa, prm, st), true;
+    if (R == 4) return go<DT, V, 4, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
+    if (R == 8) return go<DT, V, 8, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
+    if (R == 16) return go<DT, V, 16, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
     if constexpr (RawAccess<DT, V>::kBytes == 16) {
-        if (R == 20) return go<DT, V, 20, 0, BM>(u, zs, dzdx, g, sa, prm, st), true;
-        if (R == 24) return go<DT, V, 24, 0, BM>(u, zs, dzdx, g, sa, prm, st), true;
-        if (R == 32) return go<DT, V, 24, 8, BM>(u, zs, dzdx, g, sa, prm, st), true;
+        if (R == 20) return go<DT, V, 20, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
+        if (R == 24) return go<DT, V, 24, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
+        if (R == 32) return go<DT, V, 24, 8, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
     }
     return false;
 }
 
 template <int DT, int BM>
-bool launch_dt(int vec, const void* u, const void* zs, void* dzdx, const TileGeom& g, int R,
-               const SliceArgs& sa, const BwdParams& prm, hipStream_t st) {
+bool launch_dt(int vec, bool fine, const void* u, const void* zs, void* dzdx, const TileGeom& g,
+               int R, const SliceArgs& sa, const BwdParams& prm, hipStream_t st) {
     constexpr int W = 16 / static_cast<int>(sizeof(typename Elem<DT>::T));
-    if (vec == W) return launch_v<DT, W, BM>(u, zs, dzdx, g, R, sa, prm, st);
-    if (vec == W / 2) return launch_v<DT, W / 2, BM>(u, zs, dzdx, g, R, sa, prm, st);
+    if (vec == W && fine) return launch_v<DT, W, BM, true>(u, zs, dzdx, g, R, sa, prm, st);
+    if (vec == W) return launch_v<DT, W, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
+    if (vec == W / 2) return launch_v<DT, W / 2, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
     if constexpr (W / 4 > 1) {
-        if (vec == W / 4) return launch_v<DT, W / 4, BM>(u, zs, dzdx, g, R, sa, prm, st);
+        if (vec == W / 4) return launch_v<DT, W / 4, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
     }
-    if (vec == 1) return launch_v<DT, 1, BM>(u, zs, dzdx, g, R, sa, prm, st);
+    if (vec == 1) return launch_v<DT, 1, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
     return false;
 }
 
@@ -419,11 +433,12 @@ bool launch_dt(int vec, const void* u, const void* zs, void* dzdx, const TileGeo
 // The instances of one storage type (each type is a translation unit of its
 // own: slice_bwd_f32.hip, _f16.hip, _bf16.hip).
 template <int DT>
-bool launch_bwd_slice_dt(int vec, int bm, const void* u, const void* zs, void* dzdx, const TileGeom& g, int R,
-                   const SliceArgs& sa, const BwdParams& prm, hipStream_t st) {
-    return bm == kBwdFromXZ    ? launch_dt<DT, kBwdFromXZ>(vec, u, zs, dzdx, g, R, sa, prm, st)
-           : bm == kBwdFromXhat ? launch_dt<DT, kBwdFromXhat>(vec, u, zs, dzdx, g, R, sa, prm, st)
-                            : launch_dt<DT, kBwdFromZ>(vec, u, zs, dzdx, g, R, sa, prm, st);
+bool launch_bwd_slice_dt(int vec, int bm, bool fine, const void* u, const void* zs, void* dzdx,
+                         const TileGeom& g, int R, const SliceArgs& sa, const BwdParams& prm,
+                         hipStream_t st) {
+    return bm == kBwdFromXZ     ? launch_dt<DT, kBwdFromXZ>(vec, fine, u, zs, dzdx, g, R, sa, prm, st)
+           : bm == kBwdFromXhat ? launch_dt<DT, kBwdFromXhat>(vec, fine, u, zs, dzdx, g, R, sa, prm, st)
+                                : launch_dt<DT, kBwdFromZ>(vec, fine, u, zs, dzdx, g, R, sa, prm, st);
 }
 
 }  // namespace iabn_impl

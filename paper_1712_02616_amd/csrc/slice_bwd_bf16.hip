@@ -3,7 +3,8 @@
 
 namespace iabn_impl {
 
-template bool launch_bwd_slice_dt<IABN_BF16>(int, int, const void*, const void*, void*, const TileGeom&,
-                                            int, const SliceArgs&, const BwdParams&, hipStream_t);
+template bool launch_bwd_slice_dt<IABN_BF16>(int, int, bool, const void*, const void*, void*,
+                                             const TileGeom&, int, const SliceArgs&, const BwdParams&,
+                                             hipStream_t);
 
 }  // namespace iabn_impl

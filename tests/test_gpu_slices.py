@@ -110,6 +110,31 @@ def test_recomputation(s):
     parity.test_random_shape_checkpointing(s)
 
 
+@pytest.mark.parametrize("kind", ["train", "ii", "std", "ckpt"])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 300, 9409), (2, 40, 9409), (2, 270, 5001)], ids=str)
+def test_ragged_backward_sums_lose_no_small_terms(shape, dtype, kind):
+    """dz = (2^11, 2^-14, -2^11, 2^-14) over and over: an fp32 sum of two
+    neighbours drops the small one, double holds every partial sum exactly, so
+    dbeta (and dgamma, where xhat = 1) is the exact sum."""
+    N, C, HW = shape
+    dz = torch.tensor([2.0**11, 2.0**-14, -(2.0**11), 2.0**-14]).repeat(HW // 4 + 1)[:HW]
+    dz[HW // 4 * 4:] = 0
+    dz = dz.to(TORCH_DTYPES[dtype]).cuda().expand(N, C, HW).contiguous()
+    u = torch.ones_like(dz)
+    one, zero = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda")
+    dg, db = torch.empty(C, device="cuda"), torch.empty(C, device="cuda")
+    if kind == "std":
+        iabn.iabn_std_backward(u, u.clone(), dz, one, zero, zero, one, dg, db)
+    else:
+        fn = {"train": iabn.iabn_backward, "ii": iabn.iabn_backward_ii, "ckpt": iabn.iabn_ckpt_backward}[kind]
+        fn(u, dz, one, zero, one, dg, db)
+    torch.cuda.synchronize()
+    want = N * (HW // 4) * 2 * 2.0**-14
+    assert bool((db == want).all()), (db[:4], want)
+    assert kind == "std" or bool((dg == want).all()), (dg[:4], want)
+
+
 @pytest.fixture
 def abandoning(monkeypatch):
     """The binding on the library whose fp16 slices wait for one poll only."""
