@@ -110,20 +110,20 @@ typedef struct {
     int channel_resident; /* 1: one kernel, one block per channel holding the
                              channel on chip; 0: each channel is cut into
                              blocks / C slices, by the slice-resident kernels
-                             (training entry points: one kernel, one block per
-                             slice holding it on chip) or the streaming
-                             kernels (two passes for the training entry
-                             points) */
+                             (reg_accesses > 0; training entry points: one
+                             kernel, one block per slice holding it on chip)
+                             or the streaming kernels (reg_accesses 0; two
+                             passes for the training entry points) */
     int access_bytes;     /* bytes per vector access: 16, 8, 4, 2, or the
                              element size (rows of the slice-resident kernels
                              that 16-byte accesses do not divide end in single
                              elements) */
     int threads;          /* threads per block */
-    int reg_accesses;     /* channel-resident: accesses per thread held in
-                             registers (per tensor) */
-    int lds_accesses;     /* channel-resident: further accesses per thread
-                             held in LDS (per tensor); any beyond are read
-                             twice */
+    int reg_accesses;     /* channel- and slice-resident: accesses per thread
+                             that registers have room for (per tensor) */
+    int lds_accesses;     /* channel- and slice-resident: further accesses
+                             per thread held in LDS (per tensor); any beyond
+                             are read twice */
     int strips;           /* channel-resident: strip addressing (rows of
                              whole block-wide strips) */
     int xcd_order;        /* 1: blocks on each XCD take a contiguous range of

@@ -108,6 +108,7 @@ struct SlicePlan {
     TileGeom g;
     int vec;  // elements per access
     int R;    // accesses per thread the kernel holds
+    int64_t J;  // accesses per thread of a slice
     bool fine;  // backward: every element's terms to double (slice_bwd.h)
 };
 
@@ -252,7 +253,7 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     if (P > sp.P) P = sp.P;
     if (P > kMaxSlicesOnChip) P = kMaxSlicesOnChip;
     if (P < 1 || accesses(1) <= kOneSliceMaxJ) P = 1;
-    const int64_t J = accesses(P);
+    const int64_t J = out->J = accesses(P);
     set_slices(&g, P);
     const int* rungs = !wide ? kSliceNarrowRungs : backward ? kSliceBwdRungs : kSliceFwdRungs;
     const int n = !wide      ? int(sizeof kSliceNarrowRungs / sizeof(int))
@@ -615,7 +616,13 @@ int iabn_plan(int op, int dtype, int64_t N, int64_t C, int64_t HW, iabn_plan_t* 
     } else {
         plan->threads = kThreads;
         plan->blocks = C * static_cast<int64_t>(route == Route::kSlice ? sl.g.P : g.P);
-        if (route == Route::kSlice) plan->access_bytes = sl.vec * eb;
+        if (route == Route::kSlice) {
+            const int lds = slice_lds_accesses(sl.R, sl.vec * eb == 16, backward);
+            const int64_t past = sl.J - (sl.R - lds);
+            plan->access_bytes = sl.vec * eb;
+            plan->reg_accesses = sl.R - lds;
+            plan->lds_accesses = static_cast<int>(past < 0 ? 0 : past < lds ? past : lds);
+        }
         if (!train && plan_pointwise(N, C, HW, eb, vec, op == IABN_OP_CKPT_RECOMPUTE, &sl))
             plan->access_bytes = sl.vec * eb;
     }

@@ -263,6 +263,13 @@ inline bool launch_bwd_slice(int dtype, int vec, int bm, bool fine, const void* 
 constexpr int kSliceFwdRungs[] = {4, 8, 16, 20, 24, 32, 50};
 constexpr int kSliceBwdRungs[] = {4, 8, 16, 20, 24, 32};
 constexpr int kSliceNarrowRungs[] = {4, 8, 16};
+// Of the last rungs, in LDS.
+constexpr int kSliceFwdLds = 18;
+constexpr int kSliceBwdLds = 8;
+
+constexpr int slice_lds_accesses(int R, bool wide, bool backward) {
+    return !wide ? 0 : backward ? (R == 32 ? kSliceBwdLds : 0) : (R == 50 ? kSliceFwdLds : 0);
+}
 
 // False if no kernel is built for the plan's (T, R) (a planning bug).
 bool launch_fwd_fused(int dtype, int fm, void* xz, const Geom& g, const FusedPlan& fp,

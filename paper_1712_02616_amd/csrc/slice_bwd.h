@@ -409,7 +409,8 @@ bool launch_v(const void* u, const void* zs, void* dzdx, const TileGeom& g, int 
     if constexpr (RawAccess<DT, V>::kBytes == 16) {
         if (R == 20) return go<DT, V, 20, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
         if (R == 24) return go<DT, V, 24, 0, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
-        if (R == 32) return go<DT, V, 24, 8, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
+        if (R == 32)
+            return go<DT, V, 32 - kSliceBwdLds, kSliceBwdLds, BM, FINE>(u, zs, dzdx, g, sa, prm, st), true;
     }
     return false;
 }

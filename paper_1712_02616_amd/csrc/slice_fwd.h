@@ -396,7 +396,7 @@ bool launch_v(void* xz, const TileGeom& g, int R, const SliceArgs& sa, const Fwd
         if (R == 20) return go<DT, V, 20, 0, FM>(xz, g, sa, prm, st), true;
         if (R == 24) return go<DT, V, 24, 0, FM>(xz, g, sa, prm, st), true;
         if (R == 32) return go<DT, V, 32, 0, FM>(xz, g, sa, prm, st), true;
-        if (R == 50) return go<DT, V, 32, 18, FM>(xz, g, sa, prm, st), true;
+        if (R == 50) return go<DT, V, 50 - kSliceFwdLds, kSliceFwdLds, FM>(xz, g, sa, prm, st), true;
     }
     return false;
 }

@@ -38,6 +38,14 @@ def streaming(p, access=16, xcd=0, blocks=None):
         assert p["blocks"] == blocks, p
 
 
+def sliced(p, blocks, R, lds=0, access=16, xcd=0):
+    """Slice-resident: one kernel, `blocks` slices, R + lds accesses per thread held."""
+    assert p["channel_resident"] == 0 and p["threads"] == 256, p
+    assert p["channels_per_block"] == p["strips"] == 0, p
+    assert (p["blocks"], p["reg_accesses"], p["lds_accesses"]) == (blocks, R, lds) and R > 0, p
+    assert p["access_bytes"] == access and p["xcd_order"] == xcd, p
+
+
 @pytest.mark.parametrize("op", ["forward_train", "backward"])
 def test_backbone_sweep_layers(op):
     """The four layer shapes of the benchmark's sweep (fp16, N = 8)."""
@@ -99,23 +107,25 @@ def test_parity_workloads():
     # lines); 2048 channels: the forward takes one wave per channel.
     fused(plan("forward_train", BF16, 16, 2048, 28 * 28), 64, 32, strips=0, xcd=1, blocks=2048)
     fused(plan("backward", BF16, 16, 2048, 28 * 28), 256, 8, strips=0, xcd=1, blocks=2048)
-    # Tiny layer: streaming.
-    streaming(plan("forward_train", F32, 2, 16, 8 * 8))
+    # Tiny layer: one slice per channel.
+    sliced(plan("forward_train", F32, 2, 16, 8 * 8), 16, 4)
+    sliced(plan("backward", F32, 2, 16, 8 * 8), 16, 4)
 
 
 def test_few_channel_rule():
     # Forward from 64 channels, backward from 96, while a channel fits.
     fused(plan("forward_train", F16, 32, 64, 56 * 56), 1024, 16)
-    streaming(plan("backward", F16, 32, 64, 56 * 56))
+    sliced(plan("backward", F16, 32, 64, 56 * 56), 64 * 8, 8)
     fused(plan("backward", F16, 32, 96, 56 * 56), 1024, 11, lds=2)
-    streaming(plan("forward_train", F16, 32, 63, 56 * 56))
+    sliced(plan("forward_train", F16, 32, 63, 56 * 56), 63 * 8, 8)
     # Up to 16K accesses below 128 channels, 32K from 128.
-    streaming(plan("forward_train", F16, 8, 96, 256 * 256 // 2))
+    sliced(plan("forward_train", F16, 8, 96, 256 * 256 // 2), 96 * 5, 32)
     fused(plan("forward_train", F32, 32, 128, 56 * 56), 1024, 16, lds=9)
-    streaming(plan("forward_train", F16, 8, 128, 36864))
-    # A stem-like layer (64 channels of 256x256) stays on the streaming kernels.
-    streaming(plan("forward_train", F16, 8, 64, 256 * 256), blocks=64 * 8)
-    streaming(plan("backward", F16, 8, 64, 256 * 256), blocks=64 * 8)
+    sliced(plan("forward_train", F16, 8, 128, 36864), 128 * 4, 32, lds=4)
+    # A stem-like layer (64 channels of 256x256): slices, the backward's past
+    # the registers in LDS.
+    sliced(plan("forward_train", F16, 8, 64, 256 * 256), 64 * 8, 32)
+    sliced(plan("backward", F16, 8, 64, 256 * 256), 64 * 8, 24, lds=8)
 
 
 def test_rungs():
@@ -153,9 +163,9 @@ def test_comparison_blocks():
     fused(plan("ckpt_backward", F16, 8, 256, 128 * 128), 1024, 11, lds=4, strips=1)
     fused(plan("std_forward", F16, 8, 1024, 64 * 64), 256, 16, strips=1, cpb=2)
     fused(plan("ckpt_forward", F16, 8, 1024, 64 * 64), 256, 16, strips=1, cpb=2)
-    # Narrow rows: the comparison blocks take the streaming kernels.
-    streaming(plan("std_forward", F16, 32, 2048, 7 * 7), access=2, xcd=1)
-    streaming(plan("ckpt_backward", F16, 32, 2048, 7 * 7), access=2, xcd=1)
+    # Narrow rows: the comparison blocks have no channel-resident kernels.
+    sliced(plan("std_forward", F16, 32, 2048, 7 * 7), 2048, 8, access=2, xcd=1)
+    sliced(plan("ckpt_backward", F16, 32, 2048, 7 * 7), 2048, 8, access=2, xcd=1)
 
 
 def test_always_streaming_entry_points():
@@ -171,7 +181,6 @@ def test_always_streaming_entry_points():
     streaming(plan("forward_eval", F16, 8, 128, 128 * 128), blocks=4096)
     streaming(plan("forward_eval", F16, 8, 256, 128 * 128), blocks=512)
     streaming(plan("ckpt_recompute", F16, 8, 64, 256 * 256), blocks=512)
-    streaming(plan("forward_train", F16, 8, 64, 256 * 256), blocks=512)
 
 
 def test_access_width_and_xcd_order():
