@@ -183,6 +183,18 @@ bool make_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, int lanes, bo
     return true;
 }
 
+// The tiles of 64 or 256 threads, whichever leave fewer of them without an
+// access.
+bool best_tiles(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool heads, TileGeom* g) {
+    TileGeom a, b;
+    const bool ok64 = make_tiles(N, C, HW, eb, vec, 64, heads, &a);
+    const bool ok256 = make_tiles(N, C, HW, eb, vec, kThreads, heads, &b);
+    const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
+    const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
+    if (ok64 || ok256) *g = slots64 < slots256 ? a : b;
+    return ok64 || ok256;
+}
+
 // Cuts the channels into P slices.
 void set_slices(TileGeom* g, int64_t P) {
     g->P = static_cast<uint32_t>(P);
@@ -236,13 +248,7 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     const bool heads = ragged && row_heads(HW, eb, vec);
     const int v = ragged ? 16 / eb : vec;
     const bool wide = v * eb == 16;
-    TileGeom a, b;
-    const bool ok64 = make_tiles(N, C, HW, eb, v, 64, heads, &a);
-    const bool ok256 = make_tiles(N, C, HW, eb, v, kThreads, heads, &b);
-    if (!ok64 && !ok256) return false;
-    const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
-    const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
-    out->g = slots64 < slots256 ? a : b;
+    if (!best_tiles(N, C, HW, eb, v, heads, &out->g)) return false;
     out->vec = v;
     TileGeom& g = out->g;
     out->fine = ragged;
@@ -287,13 +293,7 @@ bool plan_pointwise(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool reco
     if (!ragged && (!recompute || vec * eb != 16 || C >= kPointMaxChannels)) return false;
     const bool heads = ragged && row_heads(HW, eb, vec);
     out->vec = 16 / eb;
-    TileGeom a, b;
-    const bool ok64 = make_tiles(N, C, HW, eb, out->vec, 64, heads, &a);
-    const bool ok256 = make_tiles(N, C, HW, eb, out->vec, kThreads, heads, &b);
-    if (!ok64 && !ok256) return false;
-    const int64_t slots64 = ok64 ? int64_t(a.tiles) * 64 : INT64_MAX;
-    const int64_t slots256 = ok256 ? int64_t(b.tiles) * kThreads : INT64_MAX;
-    out->g = slots64 < slots256 ? a : b;
+    if (!best_tiles(N, C, HW, eb, out->vec, heads, &out->g)) return false;
     set_slices(&out->g,
                split_channel(N * HW, C, recompute ? kTargetBlocks : eval_target_blocks(C)).P);
     return ragged || out->g.tiles >= kPointMinJ * out->g.step;
