@@ -116,12 +116,8 @@ struct SlicePlan {
 // tensors aligned to no more) move in 16-byte accesses at element alignment
 // (ragged rows, tile.h).
 constexpr int64_t kRaggedMinRowBytes = kLineBytes;
-// Channels of more values than this take the slice-resident kernels where
-// rows are ragged; smaller ones fit the channel-resident kernels' narrow
-// accesses, whose code is shorter: (8, 512, 21x21) fp16 (3528 values) 6.4 /
-// 7.9 us against 5.6 / 6.3, (8, 1024, 27x27) (5832) 10.4 / 13.9 against 12.0
-// / 15.0, (8, 512, 65x65) 16.7 / 23.2 against 28.3 / 38.0, (8, 256, 129x129)
-// 32.6 / 42.3 against 115 / 143.
+// The fewest values of a channel that few-channel layers of ragged rows move
+// in slices; smaller ones are one slice of a few narrow accesses per thread.
 constexpr int64_t kRaggedMinChannel = 4096;
 
 // Rows that 8-byte accesses divide do so only in channels larger than the
@@ -209,40 +205,136 @@ void set_slices(TileGeom* g, int64_t P) {
 }
 
 // Blocks of the slice-resident kernels that the chip holds at once: two per
-// CU (their registers and LDS, slice_bwd.hip).
+// CU (their registers and LDS, slice_bwd.h).
 constexpr int64_t kSliceBlocks = 2 * kCUs;
 static_assert(kSliceWords * sizeof(uint64_t) <= kWaves * sizeof(Partial),
               "a slice's words fit where the streaming kernels keep its partials");
 
-// Where the slice-resident kernels are the better choice (J: 16-byte accesses
-// per thread of a slice, or narrower ones; fp16 unless noted, forward /
-// backward us, against the streaming kernels' two launches, both in a graph).
-// One slice per channel while a thread has at most kOneSliceMaxJ accesses:
-// one launch and no exchange, (2, 16, 8x8) fp32 3.7 / 3.6 against 4.9 / 4.5,
-// (4, 48, 40x40) fp32 J = 5 6.5 / 7.1 against 7.1 / 7.3; J = 8 (2, 16, 64x64)
-// fp32 6.5 / 7.5 against 5.7 / 6.5.  (Few small channels of narrow accesses
-// stay on the streaming kernels, where the training entry points give the
-// same bits as their two phases.)  More slices, as many as the chip holds,
-// from kSlicesMinJ accesses on, where the second read saved is worth the
-// exchange: (32, 64, 56x56) backward J = 6 14.5 against 15.6, (8, 20,
-// 224x224) J = 8 13.3 / 15.6 against 16.9 / 21.6; but (16, 32, 56x56) J = 1.5
-// 8.6 / 9.1 against 7.7 / 8.6.  The exchange of many slices takes longer
-// (more than kFewSlices: (1, 8, 512x512) fp32 J = 4 12.2 / 12.2 against 10.0
-// / 12.0, (2, 8, 1024x1024) J = 16 22.0 / 28.8 against 22.0 / 30.6).  There is
-// no upper bound for 16-byte accesses ((64, 64, 224x224) fp32, J = 392: 395 /
-// 652 against 421 / 697); narrower ones are held 16 deep and gain up to about
-// twice that ((16, 32, 110x110) 13.5 / 15.3 against 14.1 / 16.7, (64, 64,
-// 110x110) J = 47 77.8 / 108 against 58.2 / 86.3).
+// Where the slice-resident kernels are the better choice.  Times are us,
+// forward / backward, other kernels -> slice-resident, each in a graph; J is
+// the accesses per thread of a slice.
+//
+// Against the streaming kernels' two launches.  One slice per channel needs
+// no exchange: few-channel layers of up to kOneSliceMaxJ 16-byte accesses per
+// thread ((2, 16, 8x8) fp32 4.9 / 4.5 -> 3.7 / 3.6, (1, 15, 11456) fp16 J = 6
+// 6.6 / 6.8 -> 5.9 / 6.2, but J = 8 (2, 16, 64x64) fp32 5.7 / 6.5 -> 6.5 /
+// 7.5), and of no more than kOneSliceRowJ times the accesses in a short row
+// ((279, 2, 8) fp16 J = 2 6.4 / 6.2 -> 4.9 / 5.1, (273, 2, 16) J = 3 6.5 / 6.6
+// -> 5.3 / 5.7, but (554, 9, 8) bf16 J = 3 7.1 / 7.2 -> 8.2 / 9.2).  Few small
+// channels of narrow accesses stay on the streaming kernels, where the
+// training entry points give the same bits as their two phases.
+//
+// More slices are worth their exchange where a second read is slow: the
+// blocks more than fill the CUs once, and J is at least kSlicesMinJ ((32, 25,
+// 4512) fp32 J = 8 12.4 / 15.0 -> 11.2 / 12.9, (2698, 40, 48) fp16 J = 6 12.1
+// / 14.3 -> 12.3 / 15.5, but 40 blocks (300, 1, 108) fp32 J = 5 6.8 / 7.3 ->
+// 7.8 / 7.9), or kManySlicesMinJ with more than kFewSlices, whose exchange
+// takes longer ((1, 8, 512x512) fp32 J = 4 10.0 / 12.0 -> 12.2 / 12.2).  There
+// is no upper bound for 16-byte accesses ((64, 64, 224x224) fp32, J = 392: 421
+// / 697 -> 395 / 652), except where the forward reads nearly everything twice
+// and a third of the places stays empty ((8, 171, 260x260) fp16 J = 133, 342
+// blocks: 98.7 -> 107.7).  Narrower accesses are worth it in the backward only,
+// on a full chip ((3895, 20, 60) fp16 J = 10 14.5 / 17.1 -> 14.9 / 16.8, (3055,
+// 25, 52) J = 9 backward 16.4 -> 15.5, but (3233, 16, 52) J = 6 11.2 / 12.6 ->
+// 12.2 / 12.5), and up to about twice the 16 they are held deep ((64, 64,
+// 110x110) fp16 in 8-byte accesses J = 47 58.2 / 86.3 -> 77.8 / 108).
 constexpr int64_t kOneSliceMaxJ = 6;
-constexpr int64_t kSlicesMinJ = 5;
+constexpr int64_t kOneSliceRowJ = 2;
+constexpr int64_t kSlicesMinJFwd = 7;
+constexpr int64_t kSlicesMinJBwd = 6;
 constexpr int64_t kFewSlices = 32;
 constexpr int64_t kManySlicesMinJ = 16;
+constexpr int64_t kLongSliceJ = 100;
+constexpr int64_t kLongSliceMinBlocks = 352;
+constexpr int64_t kSliceNarrowMinJBwd = 7;
 constexpr int64_t kSliceNarrowMaxJ = 32;
 
+// Ragged rows, which the streaming kernels move in narrower accesses (Jn of
+// them per thread), take slices whatever their size ((1, 64, 513x513) fp16
+// 31.7 / 44.1 -> 19.8 / 24.2), except: fewer than a batch of accesses under a
+// long exchange (more than kSomeSlices slices and Jn <= 4: (612, 7, 124) fp16
+// 8.1 / 8.7 -> 8.8 / 9.0; Jn = 8 (3, 18, 22326) fp32 9.7 / 11.2 -> 8.7 / 9.3);
+// the forward of more than kFewSlices ((2, 3, 103486) fp16 Jn = 8 8.6 -> 9.9,
+// (264, 1, 1201) fp16 Jn = 32 64 blocks 10.1 -> 10.8, (164, 1, 2377) fp32 Jn =
+// 28 10.0 -> 10.9; but with more blocks than CUs (3428, 12, 99) fp16 Jn = 32
+// 15.2 -> 13.1, (4, 7, 77177) fp32 Jn = 20 12.5 -> 12.2); and with few channels
+// one short slice with more edge elements than a thread keeps ((98, 81, 95)
+// fp16 J = 5, the standard block's backward 8.9 -> 11.6).
+constexpr int64_t kSomeSlices = 16;
+constexpr int64_t kRaggedMinNarrow = 4;
+constexpr int64_t kRaggedManyMinNarrow = 16;
+constexpr int64_t kRaggedManyMinNarrowFewBlocks = 48;
+
+int64_t edge_rounds_of(const TileGeom& g) {
+    const int64_t per_round = int64_t(g.P) * kThreads;
+    return (int64_t(g.edges) + per_round - 1) / per_round;
+}
+
+// ab: bytes of the streaming kernels' accesses.
+bool slices_over_streaming(const SlicePlan& sl, int64_t N, int64_t C, int64_t HW, int eb, int ab,
+                           bool ragged, bool backward) {
+    const int64_t P = sl.g.P, J = sl.J, blocks = C * P;
+    if (ragged) {
+        if (C < kFusedMinChannels && N * HW <= kRaggedMinChannel) return false;
+        if (P == 1)
+            return C >= kFusedMinChannels || J > kOneSliceMaxJ || edge_rounds_of(sl.g) <= kEdges;
+        const int64_t narrow = J * 16 / ab;
+        if (P > kSomeSlices && narrow <= kRaggedMinNarrow) return false;
+        return backward || P <= kFewSlices ||
+               narrow > (blocks > kCUs ? kRaggedManyMinNarrow : kRaggedManyMinNarrowFewBlocks);
+    }
+    if (ab != 16 && J > kSliceNarrowMaxJ) return false;
+    if (P == 1) {
+        if (C >= kFusedMinChannels) return true;
+        return ab == 16 && J <= kOneSliceMaxJ && J <= kOneSliceRowJ * (HW * eb / 16);
+    }
+    if (ab == 16 && P > kFewSlices) return J >= kManySlicesMinJ;
+    if (blocks <= kCUs) return false;
+    if (ab == 16)
+        return backward ? J >= kSlicesMinJBwd
+                        : J >= kSlicesMinJFwd && (J <= kLongSliceJ || blocks >= kLongSliceMinBlocks);
+    return backward && J >= kSliceNarrowMinJBwd;
+}
+
+// Ragged rows that the channel-resident kernels would move in `vchan` narrow
+// accesses per channel, whose code is shorter.  Below kFusedMinChannels they
+// are the better choice while a channel fits their registers ((1, 128, 4227)
+// fp32 4.8 / 5.7 -> 5.4 / 6.2, two slices (8, 180, 33x33) fp32 7.3 / 8.9 -> 8.9
+// / 10.2; but one slice (8, 180, 33x33) fp16 7.6 / 8.4 -> 6.8 / 7.5, three
+// (23, 133, 937) fp16 11.9 / 13.8 -> 9.3 / 10.3), above only the smallest ((1,
+// 853, 5554) bf16 7.6 / 10.3 -> 8.1 / 10.3, (10, 914, 503) fp16 11.3 / 13.2 ->
+// 9.2 / 13.0, (8, 512, 65x65) 28.3 / 38.0 -> 16.7 / 23.2).  More edge elements
+// than a thread keeps (rounds of them) change that: (98, 81, 95) fp16 9310
+// accesses, three rounds 7.4 / 8.6 -> 8.4 / 10.1, (155, 211, 167) 25885, three
+// 15.5 / 18.4 -> 13.6 / 16.2, (219, 750, 43) fp32 9417, three 23.4 / 30.4 ->
+// 21.5 / 35.9, (250, 474, 69) bf16 17250, five 16.0 / 20.9 -> 18.1 / 25.5, (542,
+// 559, 91) bf16 49322, seven 68.9 / 97.2 -> 50.8 / 81.9.  So do rows of few
+// elements ((898, 283, 39) fp32 37.1 / 51.1 -> 50.1 / 67.7, (399, 244, 69) bf16
+// backward 20.4 -> 23.3).
+constexpr int64_t kRaggedMinRowFwd = 40;
+constexpr int64_t kRaggedMinRowBwd = 72;
+constexpr int64_t kRaggedOneSliceMinAccesses = 8192;
+constexpr int64_t kRaggedSlicesMinAccesses = 20480;
+constexpr int64_t kRaggedManyChannelsMinAccesses = 4096;
+constexpr int64_t kRaggedEdgesMinAccesses = 8192;
+constexpr int64_t kRaggedMaxEdgeRounds = 4;
+constexpr int64_t kRaggedAnyEdgesMinAccesses = 32768;
+
+bool slices_over_channels(const SlicePlan& sl, int64_t C, int64_t HW, int64_t vchan, int eb,
+                          bool backward) {
+    if (HW < (backward ? kRaggedMinRowBwd : kRaggedMinRowFwd)) return false;
+    const int64_t rounds = edge_rounds_of(sl.g);
+    if (vchan > kRaggedAnyEdgesMinAccesses) return true;
+    if (C < kFusedMinChannels)
+        return sl.g.P == 1 ? rounds <= 1 && vchan > kRaggedOneSliceMinAccesses
+                           : rounds <= kRaggedMaxEdgeRounds && vchan > kRaggedSlicesMinAccesses;
+    if (rounds <= kEdges) return vchan > kRaggedManyChannelsMinAccesses;
+    return vchan > kRaggedEdgesMinAccesses && rounds <= kRaggedMaxEdgeRounds &&
+           !(backward && eb == 4);
+}
+
 // The slice-resident kernels for a layer whose aligned accesses are `vec`
-// elements wide, or false where the streaming kernels are the better choice.
-// Ragged rows take them whatever their size (the channel-resident and the
-// streaming kernels would move them in 2- or 4-byte accesses).
+// elements wide (false: none are built for it).
 bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward, SlicePlan* out) {
     const bool ragged = ragged_rows(N, HW, eb, vec);
     const bool heads = ragged && row_heads(HW, eb, vec);
@@ -268,35 +360,43 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     out->R = rungs[n - 1];
     for (int i = n - 1; i >= 0; --i)
         if (J <= rungs[i]) out->R = rungs[i];
-    if (ragged && N * HW > kRaggedMinChannel) return true;
-    if (!wide && J > kSliceNarrowMaxJ) return false;
-    if (P > 1) return J >= (P <= kFewSlices ? kSlicesMinJ : kManySlicesMinJ);
-    return C >= kFusedMinChannels || (vec * eb == 16 && J <= kOneSliceMaxJ);
+    return true;
 }
 
 // The passes without a reduction by tiles (pointwise_kernel), or false where
-// the general mapping is the better choice (us, before -> after): ragged rows
-// always (inference (8, 256, 129x129) fp16 36.3 -> 31.1, (8, 512, 65x65) 19.0
-// -> 18.0, (16, 300, 33x33) fp32 12.5 -> 11.5; the recomputation 143 -> 30.8,
-// 73 -> 18.2, 24.8 -> 11.9); of the other rows the recomputation in 16-byte
-// accesses, with fewer channels than kPointMaxChannels (each is then cut into
-// slices or has a long one) and kPointMinJ accesses per thread ((8, 256,
-// 128x128) fp16 30.8 -> 26.1, (8, 64, 256x256) 32.4 -> 25.6, (32, 256, 56x56)
-// fp32 43.0 -> 36.3; but (8, 1024, 64x64) 24.2 -> 25.0, (16, 2048, 28x28)
-// 22.0 -> 22.3, (2, 16, 8x8) 2.1 -> 2.2).
-constexpr int64_t kPointMaxChannels = 1024;
+// the general mapping is the better choice (us, before -> after).  The
+// inference forward on ragged rows ((8, 256, 129x129) fp16 36.3 -> 31.1, (8,
+// 512, 65x65) 19.0 -> 18.0, (16, 300, 33x33) fp32 12.5 -> 11.5).  The
+// recomputation on ragged rows, from more than kPointRaggedMinNarrow of the
+// general mapping's accesses per thread (143 -> 30.8, 73 -> 18.2, 24.8 ->
+// 11.9; (1, 190, 1745) fp16 eight 3.5 -> 3.4, (1, 12, 630) bf16 one 2.7 ->
+// 3.3), and of the other rows in 16-byte accesses, with long rows, fewer
+// channels than kPointMaxChannels (each is then cut into slices or has a long
+// one) and kPointMinJ accesses per thread ((8, 256, 128x128) fp16 30.8 -> 26.1,
+// (8, 64, 256x256) 32.4 -> 25.6, (32, 256, 56x56) fp32 43.0 -> 36.3, (32, 60,
+// 56x56) fp16 8.0 -> 7.8; but rows of 2704 bytes (11, 509, 1352) fp16 8.1 ->
+// 8.8, of 1088 (69, 573, 544) bf16 19.5 -> 20.6, of 80 (2937, 409, 40) 73.1 ->
+// 89.2; (3, 1008, 6168) 15.8 -> 16.4, (8, 1024, 64x64) 24.2 -> 25.0, (2, 16,
+// 8x8) 2.1 -> 2.2).
+constexpr int64_t kPointMaxChannels = 768;
+constexpr int64_t kPointMinRowBytes = 6144;
 constexpr int64_t kPointMinJ = 4;
+constexpr int64_t kPointRaggedMinNarrow = 6;
 
 bool plan_pointwise(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool recompute,
                     SlicePlan* out) {
     const bool ragged = ragged_rows(N, HW, eb, vec);
-    if (!ragged && (!recompute || vec * eb != 16 || C >= kPointMaxChannels)) return false;
+    if (!ragged && (!recompute || vec * eb != 16 || C >= kPointMaxChannels ||
+                    HW * eb < kPointMinRowBytes))
+        return false;
     const bool heads = ragged && row_heads(HW, eb, vec);
     out->vec = 16 / eb;
     if (!best_tiles(N, C, HW, eb, out->vec, heads, &out->g)) return false;
     set_slices(&out->g,
                split_channel(N * HW, C, recompute ? kTargetBlocks : eval_target_blocks(C)).P);
-    return ragged || out->g.tiles >= kPointMinJ * out->g.step;
+    const int64_t tiles = out->g.tiles, step = out->g.step;
+    return ragged ? !recompute || tiles * 16 > kPointRaggedMinNarrow * vec * eb * step
+                  : tiles >= kPointMinJ * step;
 }
 
 // Workspace bytes a slice-resident launch uses.
@@ -398,11 +498,14 @@ enum class Route { kChannel, kSlice, kStream };
 Route plan_route(int64_t N, int64_t C, int64_t HW, int dtype, const Geom& g, bool backward,
                  bool narrow_ok, FusedPlan* fp, SlicePlan* sl) {
     const int eb = elem_bytes(dtype), vec = static_cast<int>(g.vec);
-    if (ragged_rows(N, HW, eb, vec) && N * HW > kRaggedMinChannel &&
-        plan_slice(N, C, HW, eb, vec, backward, sl))
-        return Route::kSlice;
-    if (plan_fused(C, g, eb, backward, narrow_ok, fp)) return Route::kChannel;
-    return plan_slice(N, C, HW, eb, vec, backward, sl) ? Route::kSlice : Route::kStream;
+    const bool ragged = ragged_rows(N, HW, eb, vec);
+    const bool channel = plan_fused(C, g, eb, backward, narrow_ok, fp);
+    const Route other = channel ? Route::kChannel : Route::kStream;
+    if ((channel && !ragged) || !plan_slice(N, C, HW, eb, vec, backward, sl)) return other;
+    const bool slices =
+        channel ? slices_over_channels(*sl, C, HW, g.vchan, eb, backward)
+                : slices_over_streaming(*sl, N, C, HW, eb, vec * eb, ragged, backward);
+    return slices ? Route::kSlice : other;
 }
 
 const char* fwd_name(int fm) {

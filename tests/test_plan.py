@@ -242,3 +242,72 @@ def test_narrower_accesses_change_the_plan():
     streaming(plan("std_backward", F16, 8, 1024, 4100), access=8, xcd=1)
     fused(plan("forward_train", F16, 8, 1024, 4096), 256, 16, strips=1, cpb=2)
     fused(plan("forward_train", F16, 8, 1024, 4100), 1024, 16, lds=0, access=8, xcd=1)
+
+
+# Both sides of each line of the choice between the slice-resident and the
+# other kernels: (op, dtype, N, C, HW) and the (blocks, R) of the slices, "st"
+# for streaming, "cr" for channel-resident.
+ALL = ("forward_train", "backward", "std_forward", "std_backward", "ckpt_forward", "ckpt_backward")
+CHOICES = [
+    # One slice per channel: up to 6 accesses per thread, on short rows up to
+    # twice those of a row.
+    (ALL, F16, 1, 15, 11456, (15, 8)),
+    (ALL, F32, 4, 48, 1600, "st"),
+    (ALL, F16, 273, 2, 16, (2, 4)),
+    (ALL, BF16, 554, 9, 8, "st"),
+    # More slices: from 7 (backward 6) accesses on a full chip, 16 where the
+    # exchange is long.
+    (ALL, F32, 32, 25, 4512, (500, 8)),
+    (("forward_train",), F16, 2698, 40, 48, "st"),
+    (("backward",), F16, 2698, 40, 48, (480, 8)),
+    (ALL, F32, 300, 1, 108, "st"),
+    (ALL, F32, 1, 8, 512 * 512, "st"),
+    (ALL, F16, 2, 8, 1024 * 1024, (512, 16)),
+    # Far past the registers with a third of the places empty.
+    (("forward_train", "std_forward"), F16, 8, 171, 260 * 260, "st"),
+    (("forward_train", "std_forward"), F16, 8, 180, 65536, (360, 32)),
+    # Accesses below 16 bytes that divide the rows: the backward only; many
+    # channels have no other way in the comparison blocks.
+    (("forward_train",), F16, 3055, 25, 52, "st"),
+    (("backward", "ckpt_backward"), F16, 3055, 25, 52, (500, 16)),
+    (ALL, F16, 3233, 16, 52, "st"),
+    (("std_forward", "ckpt_backward"), F16, 4, 300, 2044, (300, 8)),
+    (("std_forward", "ckpt_backward"), F16, 20, 300, 2044, "st"),
+    # Ragged rows against the streaming kernels: small channels, few accesses
+    # under a long exchange, the longest exchange, more edges than are kept.
+    (("forward_train", "std_backward"), F32, 1, 16, 4097, (16, 4)),
+    (ALL, F32, 1, 16, 4095, "st"),
+    (ALL, F16, 612, 7, 124, "st"),
+    (ALL, F32, 3, 18, 22326, (306, 4)),
+    (("forward_train",), F16, 264, 1, 1201, "st"),
+    (("backward",), F16, 264, 1, 1201, (64, 4)),
+    (("forward_train",), F32, 4, 7, 77177, (448, 8)),
+    (("std_backward",), F16, 98, 81, 95, "st"),
+    # Against the channel-resident kernels: one slice, several, many channels,
+    # edges, short rows.
+    (("forward_train", "backward"), F16, 8, 180, 1089, (180, 8)),
+    (("forward_train", "backward"), F16, 7, 180, 1089, "cr"),
+    (("forward_train", "backward"), F32, 8, 180, 1089, "cr"),
+    (("std_forward", "std_backward"), F32, 8, 180, 1089, (360, 8)),
+    (("forward_train", "backward"), F16, 23, 133, 937, (399, 4)),
+    (("forward_train", "backward"), BF16, 1, 853, 5554, "cr"),
+    (("forward_train", "backward"), F16, 10, 914, 503, (914, 4)),
+    (("forward_train", "backward"), F16, 155, 211, 167, (422, 8)),
+    (("forward_train",), F32, 219, 750, 43, (750, 16)),
+    (("backward",), F32, 219, 750, 43, "cr"),
+    (("forward_train", "backward"), BF16, 250, 474, 69, "cr"),
+    (("forward_train", "backward"), BF16, 542, 559, 91, (559, 24)),
+    (("forward_train", "backward"), F32, 898, 283, 39, "cr"),
+    (("forward_train",), BF16, 399, 244, 69, (488, 8)),
+    (("backward",), BF16, 399, 244, 69, "cr"),
+]
+
+
+@pytest.mark.parametrize("ops, dtype, N, C, HW, want", CHOICES,
+                         ids=lambda v: v if isinstance(v, str) else None)
+def test_slice_choices(ops, dtype, N, C, HW, want):
+    for op in ops:
+        p = plan(op, dtype, N, C, HW)
+        got = ("cr" if p["channel_resident"] else
+               (p["blocks"], p["reg_accesses"]) if p["reg_accesses"] else "st")
+        assert got == want, (op, p)
