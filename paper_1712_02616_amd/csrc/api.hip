@@ -5,11 +5,13 @@
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
+#include <sys/random.h>
+#include <time.h>
+#include <unistd.h>
 
 #include <atomic>
 #include <cmath>
 #include <mutex>
-#include <random>
 
 #include "launch.h"
 #include "tile.h"
@@ -404,15 +406,24 @@ size_t slice_workspace(const SlicePlan& p) {
     return p.g.P > 1 ? static_cast<size_t>(p.g.C) * p.g.P * kSliceWords * sizeof(uint64_t) : 0;
 }
 
+// Random bits, or where the system has none at hand the time and the process
+// (std::random_device throws there, out of a C entry point).
+uint64_t random_start() {
+    uint64_t v = 0;
+    if (getrandom(&v, sizeof v, GRND_NONBLOCK) == static_cast<ssize_t>(sizeof v)) return v;
+    timespec t = {};
+    clock_gettime(CLOCK_REALTIME, &t);
+    return (static_cast<uint64_t>(t.tv_sec) * 1000000000u + static_cast<uint64_t>(t.tv_nsec)) *
+               0x9e3779b97f4a7c15ULL ^
+           static_cast<uint64_t>(getpid()) << 32;
+}
+
 // The tag and the key of one launch (tile.h): a count that is never 0 and not
 // repeated for 2^48 launches, starting at a random place so that what an
 // earlier process left in memory holds no tag of this one, and 64 bits that
 // differ in both halves from launch to launch (2^64 over the golden ratio).
 SliceArgs slice_args(void* workspace) {
-    static std::atomic<uint64_t> next{[] {
-        std::random_device rd;
-        return (static_cast<uint64_t>(rd()) << 32) ^ rd();
-    }()};
+    static std::atomic<uint64_t> next{random_start()};
     constexpr uint64_t mask = (uint64_t(1) << kTagBits) - 1;
     uint64_t n;
     do n = next.fetch_add(1, std::memory_order_relaxed);

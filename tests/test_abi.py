@@ -10,6 +10,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 import torch
@@ -125,6 +126,30 @@ def test_forward_train_validation(lib):
     assert fwd(lib, ws=ctypes.c_void_p(0x1008)) == ERR_WORKSPACE
     assert fwd(lib, ws=ctypes.c_void_p(0x1004)) == ERR_WORKSPACE
     assert b"workspace" in lib.iabn_last_error()
+
+
+@no_gpu
+def test_no_exception_leaves_an_entry_point(tmp_path):
+    """A shape that takes the slice-resident kernels, whose launches need a
+    number that no earlier process used: where the system's random device
+    cannot be opened, the call still ends with a status (here that there is no
+    GPU), and not in std::terminate."""
+    shim = tmp_path / "shim.cpp"
+    shim.write_text('#include <random>\n#include <stdexcept>\n'
+                    'void std::random_device::_M_init(const std::string&) '
+                    '{ throw std::runtime_error("no random device"); }\n')
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-o", str(tmp_path / "shim.so"), str(shim)],
+                   check=True)
+    code = ("import ctypes, sys\n"
+            "lib = ctypes.CDLL(sys.argv[1])\n"
+            "p, f, n = ctypes.c_void_p(0x1000), ctypes.c_float, ctypes.c_int64\n"
+            "rc = lib.iabn_forward_train(p, 0, p, p, p, p, p, p, f(1e-5), f(0.1), f(0.01), n(2), n(16),\n"
+            "                            n(64), p, ctypes.c_size_t(1 << 20), None)\n"
+            "print('status', rc)\n")
+    res = subprocess.run([sys.executable, "-c", code, iabn_build.LIB], capture_output=True, text=True,
+                         env=dict(os.environ, LD_PRELOAD=str(tmp_path / "shim.so")), timeout=120)
+    assert res.returncode == 0 and res.stdout.strip() == "status 6", (res.returncode, res.stdout,
+                                                                      res.stderr[-500:])
 
 
 @no_gpu
