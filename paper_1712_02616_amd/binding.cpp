@@ -63,6 +63,57 @@ Fn* entry(void* const* table, Op op) {
     return reinterpret_cast<Fn*>(table[op]);
 }
 
+// The call itself, without the GIL: takes a workspace (`own`) and launches.
+int launch(void* const* table, Op op, int code, int64_t N, int64_t C, int64_t HW, void* const (&big)[3],
+           float* const (&chan)[6], const float (&f)[3], at::Device dev, bool own, at::Tensor& ws) {
+    if (own) {
+        const size_t need =
+            entry<decltype(iabn_workspace_size)>(table, kWorkspaceSize)(N, C, HW, code);
+        ws = at::empty({static_cast<int64_t>(need ? need : 1)},
+                       at::TensorOptions().dtype(at::kByte).device(dev));
+    }
+    void* const wp = ws.defined() ? ws.data_ptr() : nullptr;
+    const size_t wb = ws.defined() ? ws.numel() * ws.element_size() : 0;
+    void* const st = c10::hip::getCurrentHIPStream(dev.index()).stream();
+    switch (op) {
+        case kForwardTrain:
+            return entry<decltype(iabn_forward_train)>(table, op)(
+                big[0], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1], f[2], N,
+                C, HW, wp, wb, st);
+        case kForwardTrainNoalloc:
+            return entry<decltype(iabn_forward_train_noalloc)>(table, op)(
+                big[0], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1], f[2], N,
+                C, HW, st);
+        case kForwardEval:
+            return entry<decltype(iabn_forward_eval)>(table, op)(
+                big[0], code, chan[0], chan[1], chan[2], chan[3], f[0], f[1], N, C, HW, st);
+        case kBackward:
+        case kBackwardII:
+            return entry<decltype(iabn_backward)>(table, op)(
+                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], f[0], f[1], N, C, HW,
+                wp, wb, st);
+        case kStdForward:
+            return entry<decltype(iabn_std_forward_train)>(table, op)(
+                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1],
+                f[2], N, C, HW, wp, wb, st);
+        case kStdBackward:
+            return entry<decltype(iabn_std_backward)>(table, op)(
+                big[0], big[1], big[2], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0],
+                f[1], N, C, HW, wp, wb, st);
+        case kCkptForward:
+            return entry<decltype(iabn_ckpt_forward_train)>(table, op)(
+                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1],
+                f[2], N, C, HW, wp, wb, st);
+        case kCkptRecompute:
+            return entry<decltype(iabn_ckpt_recompute)>(table, op)(
+                big[0], big[1], code, chan[0], chan[1], f[0], N, C, HW, st);
+        default:
+            return entry<decltype(iabn_ckpt_backward)>(table, op)(
+                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], f[0], f[1], N, C, HW,
+                wp, wb, st);
+    }
+}
+
 PyObject* call_checked(PyObject* const* args, Py_ssize_t n) {
     if (n < 2) return not_plain();
     void* const* table = static_cast<void* const*>(PyLong_AsVoidPtr(args[0]));
@@ -115,72 +166,27 @@ PyObject* call_checked(PyObject* const* args, Py_ssize_t n) {
     }
     args += s.floats;
     at::Tensor ws;
-    void* wp = nullptr;
-    size_t wb = 0;
+    bool own = false;
     if (s.workspace) {
-        if (args[0] == Py_None) {
-            const size_t need =
-                entry<decltype(iabn_workspace_size)>(table, kWorkspaceSize)(N, C, HW, code);
-            ws = at::empty({static_cast<int64_t>(need ? need : 1)},
-                           at::TensorOptions().dtype(at::kByte).device(dev));
-        } else {
+        own = args[0] == Py_None;
+        if (!own) {
             if (!THPVariable_CheckExact(args[0])) return not_plain();
             ws = THPVariable_Unpack(args[0]);
             if (ws.device() != dev || !ws.is_contiguous()) return not_plain();
         }
-        wp = ws.data_ptr();
-        wb = ws.numel() * ws.element_size();
     }
-    void* st = c10::hip::getCurrentHIPStream(dev.index()).stream();
 
+    // An allocation can wait for the device and a launch for room in the
+    // queue, so other Python threads go on meanwhile.
     int rc = 0;
-    Py_BEGIN_ALLOW_THREADS;  // a launch can wait for room in the queue
-    switch (op) {
-        case kForwardTrain:
-            rc = entry<decltype(iabn_forward_train)>(table, op)(
-                big[0], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1], f[2], N,
-                C, HW, wp, wb, st);
-            break;
-        case kForwardTrainNoalloc:
-            rc = entry<decltype(iabn_forward_train_noalloc)>(table, op)(
-                big[0], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1], f[2], N,
-                C, HW, st);
-            break;
-        case kForwardEval:
-            rc = entry<decltype(iabn_forward_eval)>(table, op)(big[0], code, chan[0], chan[1], chan[2],
-                                                               chan[3], f[0], f[1], N, C, HW, st);
-            break;
-        case kBackward:
-        case kBackwardII:
-            rc = entry<decltype(iabn_backward)>(table, op)(big[0], big[1], code, chan[0], chan[1],
-                                                           chan[2], chan[3], chan[4], f[0], f[1], N, C,
-                                                           HW, wp, wb, st);
-            break;
-        case kStdForward:
-            rc = entry<decltype(iabn_std_forward_train)>(table, op)(
-                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1],
-                f[2], N, C, HW, wp, wb, st);
-            break;
-        case kStdBackward:
-            rc = entry<decltype(iabn_std_backward)>(table, op)(
-                big[0], big[1], big[2], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0],
-                f[1], N, C, HW, wp, wb, st);
-            break;
-        case kCkptForward:
-            rc = entry<decltype(iabn_ckpt_forward_train)>(table, op)(
-                big[0], big[1], code, chan[0], chan[1], chan[2], chan[3], chan[4], chan[5], f[0], f[1],
-                f[2], N, C, HW, wp, wb, st);
-            break;
-        case kCkptRecompute:
-            rc = entry<decltype(iabn_ckpt_recompute)>(table, op)(big[0], big[1], code, chan[0], chan[1],
-                                                                 f[0], N, C, HW, st);
-            break;
-        default:
-            rc = entry<decltype(iabn_ckpt_backward)>(table, op)(big[0], big[1], code, chan[0], chan[1],
-                                                                chan[2], chan[3], chan[4], f[0], f[1], N,
-                                                                C, HW, wp, wb, st);
+    PyThreadState* thread = PyEval_SaveThread();
+    try {
+        rc = launch(table, op, code, N, C, HW, big, chan, f, dev, own, ws);
+    } catch (...) {
+        PyEval_RestoreThread(thread);
+        throw;
     }
-    Py_END_ALLOW_THREADS;
+    PyEval_RestoreThread(thread);
     return PyLong_FromLong(rc);
 }
 

@@ -5,6 +5,8 @@ for the same wrong arguments, whichever path meets them first.
 
 from __future__ import annotations
 
+import ctypes
+
 import pytest
 import torch
 
@@ -114,6 +116,22 @@ def test_workspace_arguments():
         CALLS["forward_train"](t, workspace=torch.empty(need, dtype=torch.uint8))
     with pytest.raises(iabn.IabnError, match="eps"):
         iabn.iabn_forward_train(t["x"], t["gamma"], t["beta"], t["rm"], t["rv"], t["sm"], t["sv"], eps=0.0)
+
+
+def test_other_threads_run_meanwhile():
+    """The fast path takes its workspace and launches without the GIL: with
+    entry points that report the GIL's state in place of the library's, a
+    workspace of no bytes is asked for (the address of the thread that holds
+    the GIL otherwise, too many to get) and the launch's status is 0."""
+    t = _state((2, C, 64), torch.float32)
+    CALLS["forward_train"](t)  # loads the fast path
+    addr = lambda fn: ctypes.cast(fn, ctypes.c_void_p).value  # noqa: E731
+    table = type(iabn.load().table_array)(*iabn.load().table_array)
+    table[iabn._WORKSPACE_SIZE] = addr(ctypes.pythonapi._PyThreadState_UncheckedGet)
+    table[iabn._FORWARD_TRAIN] = addr(ctypes.pythonapi.PyGILState_Check)
+    rc = iabn._call(ctypes.addressof(table), iabn._FORWARD_TRAIN, t["x"], t["gamma"], t["beta"], t["rm"],
+                    t["rv"], t["sm"], t["sv"], 1e-5, 0.1, 0.01, None)
+    assert rc == 0
 
 
 def test_current_stream():
