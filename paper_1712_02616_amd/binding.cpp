@@ -11,6 +11,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <cxxabi.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "iabn.h"
@@ -197,6 +198,8 @@ PyObject* call_checked(PyObject* const* args, Py_ssize_t n) {
 PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
     try {
         return call_checked(args, n);
+    } catch (abi::__forced_unwind&) {
+        throw;  // the interpreter ends this thread
     } catch (...) {
         return not_plain();
     }
