@@ -23,7 +23,9 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import math
+import os
 import threading
+import warnings
 
 import torch
 
@@ -86,7 +88,6 @@ def load():
         if _lib is None:
             if not _build.is_built():
                 _build.build()
-                _build.build_binding()
             _lib = declare(ctypes.CDLL(_build.LIB))
     return _lib
 
@@ -126,19 +127,29 @@ def declare(lib):
 
 
 def _first_call(*args):
-    """Loads the native fast path (building it first if it has never been
-    built) and calls it."""
+    """Loads the native fast path (building it first if it has not been built
+    for this torch and this Python) and calls it.  Without it every call is
+    marshalled by the Python code."""
     global _call
     with _lib_lock:
         if _call is _first_call:
-            if not _build.is_built():
-                _build.build()
-                _build.build_binding()
-            spec = importlib.util.spec_from_file_location(__name__ + "._binding", _build.BINDING_LIB)
-            module = importlib.util.module_from_spec(spec)
-            spec.loader.exec_module(module)
-            _call = module.call
+            try:
+                path = _build.binding_lib()
+                if not os.path.exists(path):
+                    _build.build_binding()
+                spec = importlib.util.spec_from_file_location(__name__ + "._binding", path)
+                module = importlib.util.module_from_spec(spec)
+                spec.loader.exec_module(module)
+                _call = module.call
+            except Exception as e:  # noqa: BLE001
+                warnings.warn("libiabn's native fast path is not available, calls are marshalled in "
+                              "Python: %s" % e, RuntimeWarning, stacklevel=4)
+                _call = _not_available
     return _call(*args)
+
+
+def _not_available(*args):
+    return NotImplemented
 
 
 # call(table, op, tensors..., floats...[, workspace]) -> status, or

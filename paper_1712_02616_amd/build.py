@@ -26,7 +26,6 @@ ABANDON_LIB = os.path.join(HERE, "libiabn_abandon.so")
 ABANDON_SOURCES = ("slice_fwd_f16.hip", "slice_bwd_f16.hip")
 ABANDON_FLAG = "-DIABN_SLICE_POLLS=1"
 BINDING_SRC = os.path.join(HERE, "binding.cpp")
-BINDING_LIB = os.path.join(HERE, "_binding.so")
 PROBE_SRC = os.path.join(HERE, "bench_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libiabn_probe.so")
 ARCH = "gfx950"
@@ -85,9 +84,20 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def binding_lib() -> str:
+    """The Python binding's fast path for this torch and this Python, whose
+    C++ and C interfaces it is compiled against."""
+    import sysconfig
+
+    import torch
+
+    return os.path.join(HERE, "_binding.torch-%s.%s.so" % (torch.__version__,
+                                                           sysconfig.get_config_var("SOABI")))
+
+
 def build_binding() -> str:
-    """Always recompiles _binding.so (the Python binding's fast path, host
-    code against torch's and Python's headers)."""
+    """Always recompiles the Python binding's fast path (host code against
+    torch's and Python's headers)."""
     import sysconfig
 
     import torch
@@ -96,7 +106,8 @@ def build_binding() -> str:
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
     incs = [os.path.join(ROOT, "include"), os.path.join(rocm, "include"),
             sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
-    out = BINDING_LIB + ".tmp%d" % os.getpid()
+    lib = binding_lib()
+    out = lib + ".tmp%d" % os.getpid()
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = (["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-o", out, BINDING_SRC] +
@@ -107,8 +118,8 @@ def build_binding() -> str:
     if res.returncode != 0:
         raise RuntimeError("building the binding failed (%d):\n%s\n%s"
                            % (res.returncode, " ".join(cmd), res.stderr))
-    os.replace(out, BINDING_LIB)
-    return BINDING_LIB
+    os.replace(out, lib)
+    return lib
 
 
 def build_probe() -> str:
@@ -123,7 +134,7 @@ def build_probe() -> str:
 
 
 def is_built() -> bool:
-    return os.path.exists(LIB) and os.path.exists(BINDING_LIB)
+    return os.path.exists(LIB)
 
 
 if __name__ == "__main__":

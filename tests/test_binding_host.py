@@ -7,6 +7,9 @@ import os
 import subprocess
 import sys
 
+import pytest
+import torch
+
 import paper_1712_02616_amd as iabn
 from paper_1712_02616_amd import build as iabn_build
 
@@ -36,7 +39,34 @@ last = Last()
 
 
 def test_a_thread_ends_with_the_interpreter():
-    iabn.load()
-    res = subprocess.run([sys.executable, "-c", AT_EXIT, "paper_1712_02616_amd._binding",
-                          iabn_build.BINDING_LIB], capture_output=True, text=True, cwd=ROOT, timeout=120)
+    lib = iabn_build.binding_lib()
+    if not os.path.exists(lib):
+        iabn_build.build_binding()
+    res = subprocess.run([sys.executable, "-c", AT_EXIT, "paper_1712_02616_amd._binding", lib],
+                         capture_output=True, text=True, cwd=ROOT, timeout=120)
     assert res.returncode == 0, (res.returncode, res.stderr[-500:])
+
+
+@pytest.mark.parametrize("what", ["not a library", "not built"])
+def test_calls_go_on_without_the_fast_path(what, tmp_path, monkeypatch):
+    path = tmp_path / "_binding.so"
+    if what == "not a library":
+        path.write_bytes(b"something else")
+    else:
+        def no_compiler():
+            raise RuntimeError("no compiler")
+        monkeypatch.setattr(iabn_build, "build_binding", no_compiler)
+    monkeypatch.setattr(iabn_build, "binding_lib", lambda: str(path))
+    monkeypatch.setattr(iabn, "_call", iabn._first_call)
+    x, c = torch.zeros(2, 3, 4), torch.zeros(3)
+    with pytest.warns(RuntimeWarning, match="fast path"):
+        with pytest.raises(ValueError, match="HIP device"):
+            iabn.iabn_forward_eval(x, c, c, c, c)
+    with pytest.raises(ValueError, match="HIP device"):
+        iabn.iabn_forward_eval(x, c, c, c, c)
+
+
+def test_the_fast_path_belongs_to_one_torch(monkeypatch):
+    here = iabn_build.binding_lib()
+    monkeypatch.setattr(torch, "__version__", "0.0.1")
+    assert iabn_build.binding_lib() != here
