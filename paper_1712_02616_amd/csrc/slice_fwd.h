@@ -406,11 +406,15 @@ bool launch_dt(int vec, void* xz, const TileGeom& g, int R, const SliceArgs& sa,
                const FwdParams& prm, hipStream_t st) {
     constexpr int W = 16 / static_cast<int>(sizeof(typename Elem<DT>::T));
     if (vec == W) return launch_v<DT, W, FM>(xz, g, R, sa, prm, st);
-    if (vec == W / 2) return launch_v<DT, W / 2, FM>(xz, g, R, sa, prm, st);
-    if constexpr (W / 4 > 1) {
-        if (vec == W / 4) return launch_v<DT, W / 4, FM>(xz, g, R, sa, prm, st);
+    // InPlace-ABN's own forward takes the channel-resident kernels where the
+    // comparison blocks take narrower accesses here.
+    if constexpr (FM != kFwdInPlace) {
+        if (vec == W / 2) return launch_v<DT, W / 2, FM>(xz, g, R, sa, prm, st);
+        if constexpr (W / 4 > 1) {
+            if (vec == W / 4) return launch_v<DT, W / 4, FM>(xz, g, R, sa, prm, st);
+        }
+        if (vec == 1) return launch_v<DT, 1, FM>(xz, g, R, sa, prm, st);
     }
-    if (vec == 1) return launch_v<DT, 1, FM>(xz, g, R, sa, prm, st);
     return false;
 }
 
