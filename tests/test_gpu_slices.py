@@ -39,19 +39,29 @@ def _shape(N, C, HW, dtype, offset=0):
 # accesses per thread (the last ones of each rung, and the first past it).
 RUNGS = [_shape(1, 257, J * 1024 + 1, "f32") for J in (4, 5, 9, 17, 21, 25, 33, 51)]
 # Tails of 1 to 7 elements, tiles of parts of rows.
-TAILS = [_shape(3, 40, 2048 + k, dt) for dt, ks in (("f16", (1, 2, 3, 5, 6, 7)), ("f32", (1, 2, 3)))
+TAILS = [_shape(3, 40, 2048 + k, dt) for dt, ks in (("f16", (1, 2, 3, 5, 6, 7)), ("f32", (1, 3)))
          for k in ks]
 SMALL = [
     _shape(2, 16, 64, "f32"),           # less than a tile
     _shape(100, 300, 71, "f16"),        # whole rows per tile, the last tile with fewer; long tails
     _shape(37, 270, 115, "bf16"),
     _shape(5, 7, 1041, "bf16"),
-    _shape(64, 5, 196, "f16"),          # 8-byte accesses
-    _shape(9, 11, 50, "f16"),           # 4-byte accesses, rows shorter than a line
-    _shape(40, 33, 49, "f16"),          # 2-byte accesses
     _shape(4, 30, 4096, "f16", 1),      # whole accesses at an element's alignment
     _shape(4, 30, 4096, "f32", 3),
 ]
+# Accesses of 8, 4 and 2 bytes: one slice per channel (the comparison blocks)
+# on each rung and past it, and slices that exchange sums (the backward).
+NARROW_BLOCKS = [
+    _shape(9, 300, 196, "f16"), _shape(64, 300, 100, "f16"), _shape(64, 300, 196, "bf16"),
+    _shape(150, 300, 196, "f16"),                                            # 8 bytes, past 16 accesses
+    _shape(5, 300, 50, "f16"), _shape(250, 300, 50, "bf16"),                 # 4
+    _shape(20, 300, 49, "f16"), _shape(40, 300, 49, "f16"), _shape(60, 300, 49, "bf16"),
+    _shape(130, 300, 49, "f16"),                                             # 2, past 16 accesses
+    _shape(30, 300, 30, "f32"), _shape(100, 300, 98, "f32"),                 # 8
+    _shape(20, 300, 31, "f32"), _shape(100, 300, 31, "f32"),                 # 4
+]
+NARROW_EXCHANGE = [_shape(3000, 20, 52, "f16"), _shape(3000, 20, 50, "f16"), _shape(3000, 20, 49, "bf16"),
+                   _shape(2600, 20, 30, "f32"), _shape(2600, 20, 31, "f32")]
 # Channels cut into P slices (few, many, the most) that exchange sums.
 EXCHANGE = [
     _shape(4, 40, 40000, "f16"),        # 12 slices
@@ -62,21 +72,41 @@ EXCHANGE = [
 ]
 CHECKS = [parity.test_random_shape_parity, parity.test_random_shape_backward_ii,
           parity.test_random_shape_standard_block, parity.test_random_shape_checkpointing]
-ID = lambda v: v.id if isinstance(v, parity.Shape) else v.__name__.replace("test_random_shape_", "")  # noqa: E731
+ID = lambda v: (v if isinstance(v, str) else v.id if isinstance(v, parity.Shape) else  # noqa: E731
+                v.__name__.replace("test_random_shape_", ""))
 
 
-@pytest.mark.parametrize("s", EXCHANGE + RUNGS, ids=ID)
-def test_takes_the_slices(s):
-    for op in ("forward_train", "backward"):
-        p = iabn.iabn_plan(op, TORCH_DTYPES[s.dtype], s.N, s.C, s.HW)
-        P = max(1, min(512 // s.C, 64))
-        assert p["channel_resident"] == 0 and p["reg_accesses"] > 0 and p["access_bytes"] == 16, p
-        assert p["blocks"] == s.C * P, p
+FORWARDS = ["forward_train", "std_forward", "ckpt_forward"]
+BACKWARDS = ["backward", "std_backward", "ckpt_backward"]
+BLOCKS = FORWARDS[1:] + BACKWARDS[1:]
+
+
+# (Plans are those of aligned tensors.  (100, 300, 71): InPlace-ABN's own
+# passes are channel-resident.)
+@pytest.mark.parametrize("shapes, ops", [
+    (TAILS + [s for s in SMALL if not s.offset and s.N != 100] + EXCHANGE + RUNGS, FORWARDS + BACKWARDS),
+    ([s for s in SMALL if s.N == 100] + NARROW_BLOCKS, BLOCKS),
+    (NARROW_EXCHANGE, BACKWARDS)], ids=["all", "blocks", "backwards"])
+def test_takes_the_slices(shapes, ops):
+    for s in shapes:
+        for op in ops:
+            p = iabn.iabn_plan(op, TORCH_DTYPES[s.dtype], s.N, s.C, s.HW)
+            assert p["channel_resident"] == 0 and p["reg_accesses"] > 0, (s, op, p)
+            narrow = s in NARROW_BLOCKS or s in NARROW_EXCHANGE
+            assert (p["access_bytes"] < 16) == narrow, (s, op, p)
+            exchange = s in EXCHANGE or s in NARROW_EXCHANGE
+            assert (p["blocks"] > s.C) == exchange, (s, op, p)
 
 
 @pytest.mark.parametrize("check", CHECKS, ids=ID)
-@pytest.mark.parametrize("s", TAILS + SMALL + EXCHANGE, ids=ID)
+@pytest.mark.parametrize("s", TAILS + SMALL + EXCHANGE + NARROW_EXCHANGE, ids=ID)
 def test_slices(s, check):
+    check(s)
+
+
+@pytest.mark.parametrize("check", CHECKS[2:], ids=ID)
+@pytest.mark.parametrize("s", NARROW_BLOCKS, ids=ID)
+def test_narrow_blocks(s, check):
     check(s)
 
 
