@@ -4,8 +4,8 @@ Each translation unit of ``csrc/`` compiles to an object file in parallel,
 then one link makes the shared library.  ``build_probe`` compiles the
 benchmark's bandwidth probes (``bench_probe.hip``) into a library of their
 own, ``libiabn_probe.so``; libiabn does not contain or use them.  The tests'
-``libiabn_abandon.so`` is libiabn with the fp16 slice-resident kernels built
-to wait for a single poll, so that their abandoned slices can be tested.
+``libiabn_abandon.so`` is libiabn with the fp16 and fp32 slice-resident
+kernels built to abandon every other slice (``csrc/tile.h``).
 """
 
 from __future__ import annotations
@@ -23,8 +23,8 @@ SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [os.path.join(ROOT, "include", "iabn.h")]
 LIB = os.path.join(HERE, "libiabn.so")
 ABANDON_LIB = os.path.join(HERE, "libiabn_abandon.so")
-ABANDON_SOURCES = ("slice_fwd_f16.hip", "slice_bwd_f16.hip")
-ABANDON_FLAG = "-DIABN_SLICE_POLLS=1"
+ABANDON_SOURCES = ("slice_fwd_f16.hip", "slice_bwd_f16.hip", "slice_fwd_f32.hip", "slice_bwd_f32.hip")
+ABANDON_FLAG = "-DIABN_TEST_ABANDON"
 BINDING_SRC = os.path.join(HERE, "binding.cpp")
 PROBE_SRC = os.path.join(HERE, "bench_probe.hip")
 PROBE_LIB = os.path.join(HERE, "libiabn_probe.so")
@@ -47,11 +47,12 @@ def _run(cmd):
     return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
 
 
-def build(verbose: bool = False) -> str:
-    """Always recompiles; writes libiabn.so next to this file atomically."""
+def build(verbose: bool = False, abandon: bool = False) -> str:
+    """Always recompiles; writes libiabn.so next to this file atomically.
+    abandon: the tests' libiabn_abandon.so too."""
     cc = hipcc()
     with tempfile.TemporaryDirectory(prefix="iabn_build_") as tmp:
-        objs, abandon, procs = [], [], []
+        objs, abandon_objs, procs = [], [], []
 
         def compile_(src, obj, extra=()):
             cmd = [cc] + FLAGS + list(extra) + ["-c", "-o", obj, src]
@@ -62,8 +63,8 @@ def build(verbose: bool = False) -> str:
         for src in sorted(SOURCES, key=lambda s: "slice" not in s):
             name = os.path.basename(src)
             objs.append(compile_(src, os.path.join(tmp, name + ".o")))
-            abandon.append(compile_(src, os.path.join(tmp, name + ".abandon.o"), [ABANDON_FLAG])
-                           if name in ABANDON_SOURCES else objs[-1])
+            abandon_objs.append(compile_(src, os.path.join(tmp, name + ".abandon.o"), [ABANDON_FLAG])
+                                if abandon and name in ABANDON_SOURCES else objs[-1])
         errors = []
         for cmd, p in procs:
             out, err = p.communicate()
@@ -73,7 +74,7 @@ def build(verbose: bool = False) -> str:
                 print(err)
         if errors:
             raise RuntimeError("hipcc failed:\n" + "\n".join(errors))
-        for lib, parts in ((LIB, objs), (ABANDON_LIB, abandon)):
+        for lib, parts in [(LIB, objs)] + ([(ABANDON_LIB, abandon_objs)] if abandon else []):
             out = lib + ".tmp%d" % os.getpid()
             cmd = [cc, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", out] + parts
             res = subprocess.run(cmd, capture_output=True, text=True)

@@ -305,9 +305,15 @@ constexpr uint64_t kTagBits = 64 - kTagShift;
 
 // Longest wait for the other blocks, in polls; a poll is a round trip to
 // memory, about 0.7 us, and a wait takes one to three when all blocks run.
-#ifndef IABN_SLICE_POLLS
-#define IABN_SLICE_POLLS 256
+constexpr uint32_t kPolls = 256;
+// Compiled in for tests: the odd slices of a channel give up without waiting,
+// and the last block leaves kAbandonMark in the flags of those it has written.
+#ifdef IABN_TEST_ABANDON
+constexpr bool kTestAbandon = true;
+#else
+constexpr bool kTestAbandon = false;
 #endif
+constexpr uint64_t kAbandonMark = ~uint64_t(0);  // no tag
 // The channel's last block finds all sums in its first polls.  Only calls that
 // share a workspace at the same time, which the interface forbids, can have
 // overwritten them: its wait then ends too (in under a second), the results
@@ -442,7 +448,7 @@ template <int NP>
 __device__ __forceinline__ bool slice_wait(const SliceSync& s, uint32_t p, uint64_t seen,
                                            uint32_t (&piece)[NP], uint32_t* stage, uint64_t& done) {
     done = 0;
-    if (slice_collect(s, piece, stage, IABN_SLICE_POLLS)) return true;
+    if (!(kTestAbandon && (p & 1)) && slice_collect(s, piece, stage, kPolls)) return true;
     if (lane_id() == 0) {
         agent_store(s.flag + p, s.tag);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -484,8 +490,9 @@ __device__ __forceinline__ void lds_barrier() {
 __device__ __forceinline__ void slice_abandoned(const SliceSync& s, uint32_t own,
                                                 uint32_t (&left)[kMaxSlicesOnChip]) {
     if (threadIdx.x < s.P) {
-        left[threadIdx.x] = threadIdx.x != own && agent_load(s.flag + threadIdx.x) == s.tag;
-        agent_store(s.flag + threadIdx.x, 0);
+        const bool is_left = threadIdx.x != own && agent_load(s.flag + threadIdx.x) == s.tag;
+        left[threadIdx.x] = is_left;
+        agent_store(s.flag + threadIdx.x, kTestAbandon && is_left ? kAbandonMark : 0);
     }
     __syncthreads();
 }

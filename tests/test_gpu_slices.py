@@ -1,8 +1,8 @@
 """The slice-resident kernels at the sizes where they can go wrong: each rung
 of registers and what lies past it, tiles of whole rows and of parts of rows,
 ragged rows with every tail, unaligned tensors, channels cut into slices that
-exchange their sums (also when a block gives up waiting, in a library built
-to wait for one poll only), workspaces full of garbage, graph replays and
+exchange their sums (also when blocks give up waiting, in a library built to
+abandon every other slice), workspaces full of garbage, graph replays and
 concurrent streams.  Each shape goes through the parity checks of
 test_gpu_random_shapes.py (oracle, guard bands), InPlace-ABN I and II and both
 comparison blocks.
@@ -165,18 +165,77 @@ def test_ragged_backward_sums_lose_no_small_terms(shape, dtype, kind):
     assert kind == "std" or bool((dg == want).all()), (dg[:4], want)
 
 
+# Layers whose slices are abandoned: in 16-byte accesses, with edges, and in
+# narrower ones (the backward only).
+ABANDON_WIDE = [s for s in EXCHANGE if s.dtype in ("f16", "f32")]
+ABANDON_NARROW = [s for s in NARROW_EXCHANGE if s.HW in (50, 31)]
+
+
 @pytest.fixture
 def abandoning(monkeypatch):
-    """The binding on the library whose fp16 slices wait for one poll only."""
+    """The binding on the library whose fp16 and fp32 kernels abandon the odd
+    slices of a channel."""
     if not os.path.exists(iabn_build.ABANDON_LIB):
-        iabn_build.build()
-    monkeypatch.setattr(iabn, "_lib", iabn.declare(ctypes.CDLL(iabn_build.ABANDON_LIB)))
+        iabn_build.build(abandon=True)
+    lib = iabn.declare(ctypes.CDLL(iabn_build.ABANDON_LIB))
+    monkeypatch.setattr(iabn, "_lib", lib)
+    return lib
 
 
 @pytest.mark.parametrize("check", CHECKS, ids=ID)
-@pytest.mark.parametrize("s", [s for s in EXCHANGE if s.dtype == "f16"], ids=ID)
+@pytest.mark.parametrize("s", ABANDON_WIDE + ABANDON_NARROW, ids=ID)
 def test_abandoned_slices(s, check, abandoning):
     check(s)
+
+
+def _one_op(op, L, ws):
+    """One training entry point on copies of the layer's tensors; its outputs."""
+    x, z, dz = L["x0"].clone(), L["z0"].clone(), L["dz0"].clone()
+    v = {k: L[k].clone() for k in ("rm", "rv", "sm", "sv", "dg", "db")}
+    a, kw = (L["g"], L["b"]), {"workspace": ws}
+    stats = (v["rm"], v["rv"], v["sm"], v["sv"])
+    if op == "forward_train":
+        iabn.iabn_forward_train(x, *a, *stats, **kw)
+    elif op == "std_forward":
+        iabn.iabn_std_forward_train(x, z, *a, *stats, **kw)
+    elif op == "ckpt_forward":
+        iabn.iabn_ckpt_forward_train(x, z, *a, *stats, **kw)
+    elif op == "backward":
+        iabn.iabn_backward(z, dz, *a, v["sv"], v["dg"], v["db"], **kw)
+    elif op == "std_backward":
+        iabn.iabn_std_backward(x, z, dz, *a, v["sm"], v["sv"], v["dg"], v["db"], **kw)
+    else:
+        iabn.iabn_ckpt_backward(x, dz, *a, v["sv"], v["dg"], v["db"], **kw)
+    torch.cuda.synchronize()
+    return dict(v, x=x, z=z, dz=dz)
+
+
+@pytest.mark.parametrize("s, op", [(s, op) for s in ABANDON_WIDE for op in FORWARDS + BACKWARDS] +
+                         [(s, op) for s in ABANDON_NARROW for op in BACKWARDS], ids=ID)
+def test_the_last_block_writes_abandoned_slices(s, op, abandoning, monkeypatch):
+    """Bit for bit what the slices' own blocks write, and the flags in the
+    workspace (behind the slots, 6 words twice for each slice) show that the
+    last block did write them: every odd slice but its own."""
+    plan = iabn.iabn_plan(op, TORCH_DTYPES[s.dtype], s.N, s.C, s.HW)
+    slices = plan["blocks"]
+    P = slices // s.C
+    assert plan["reg_accesses"] > 0 and P > 3, plan
+    L = test_gpu_streams._layer((s.N, s.C, s.HW), s.dtype, s.seed)
+    L["z0"] = torch.randn_like(L["x0"])
+    for k, v in dict(rm=0.0, sm=0.0, dg=0.0, db=0.0, rv=1.0, sv=1.0).items():
+        L[k].fill_(v)
+    say("abandoned %s %s" % (op, s.id))
+    got = {}
+    for name, lib in (("product", None), ("abandoning", abandoning)):
+        with monkeypatch.context() as m:
+            m.setattr(iabn, "_lib", lib)
+            L["ws"].random_(0, 256)
+            got[name] = _one_op(op, L, L["ws"])
+    for k, v in got["product"].items():
+        assert torch.equal(v, got["abandoning"][k]), k
+    words = L["ws"][:slices * 16 * 8].view(torch.int64)
+    marks = (words[slices * 12:slices * 13].view(s.C, P) == -1).sum(1)
+    assert bool((marks >= P // 2 - 1).all()) and bool((marks <= P // 2).all()), marks
 
 
 GRAPH = ((4, 40, 40000), "f16")
