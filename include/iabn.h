@@ -40,10 +40,12 @@
  *  - Tensor pointers need only the alignment of their element type.  Each
  *    call reads and writes 16-byte accesses where HW and the pointers'
  *    alignment allow, else 8-, 4- or 2-byte ones, or 16-byte ones at the
- *    alignment of an element (another width changes the order of the sums,
- *    not the result beyond rounding).
- *  - Results are deterministic: the same inputs on the same device give
- *    bit-identical outputs (all reductions combine in a fixed order).
+ *    alignment of an element, from a 16-byte boundary on where rows are long
+ *    (another width, or another address modulo 16, changes the order of the
+ *    sums, not the result beyond rounding).
+ *  - Results are deterministic: the same inputs at addresses that are equal
+ *    modulo 16, on the same device, give bit-identical outputs (all
+ *    reductions combine in a fixed order).
  *  - The workspace's content before a call does not matter (but see the
  *    phases below).  Blocks of the slice-resident kernels exchange sums
  *    through it; no block waits without bound, so calls on different streams
@@ -137,10 +139,11 @@ typedef struct {
 /* The kernels entry point `op` (an iabn_op_t) runs for this shape and
  * storage type when every tensor is 16-byte aligned.  The plan holds only
  * for such tensors: a tensor that is not takes narrower accesses, which can
- * change every field (the comparison blocks then take the streaming kernels,
- * InPlace-ABN's own entry points other rungs and block sizes).  Host only:
- * needs no GPU, launches nothing.  For callers that schedule around the library, and for tests of
- * the library's choices.  Validates like the entry point (shape, dtype; a
+ * change every field (the comparison blocks then take the slice-resident or
+ * the streaming kernels, InPlace-ABN's own entry points those or other rungs
+ * and block sizes).  Host only: needs no GPU, launches nothing.  For callers
+ * that schedule around the library, and for tests of the library's choices.
+ * Validates like the entry point (shape, dtype; a
  * NULL plan is IABN_ERR_NULL, an unknown op IABN_ERR_PARAM); an empty shape
  * gives an all-zero plan. */
 int iabn_plan(int op, int dtype, int64_t N, int64_t C, int64_t HW, iabn_plan_t *plan);

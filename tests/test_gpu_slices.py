@@ -165,6 +165,36 @@ def test_ragged_backward_sums_lose_no_small_terms(shape, dtype, kind):
     assert kind == "std" or bool((dg == want).all()), (dg[:4], want)
 
 
+@pytest.mark.parametrize("shape", [(2, 300, 9409), (2, 40, 9409)], ids=str)
+def test_alignment_moves_last_bits_only(shape):
+    """Rows of 16-bit elements whose accesses start at a 16-byte boundary: the
+    same bits at equal addresses modulo 16, else sums in another order.  A
+    run's 8 fp32 additions are each off by 2^-24 of it, so a mean moves by at
+    most 5e-7 of the values' spread and a variance by 1e-6 of itself (the
+    backward's sums, in double, by their final rounding), and outputs by a
+    rounding to storage."""
+    N, C, HW = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x0, z0, dz0 = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    one, zero = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda")
+    got = {}
+    for off in (0, 8, 1, 3, 6):
+        x, z, dz = (torch.empty(N * C * HW + 8, dtype=torch.half, device="cuda")[off:off + N * C * HW]
+                    .view(shape).copy_(t) for t in (x0, z0, dz0))
+        st = [torch.zeros(C, device="cuda") for _ in range(6)]
+        iabn.iabn_forward_train(x, one, zero, *st[:4])
+        iabn.iabn_backward(z, dz, one, zero, one, *st[4:])
+        torch.cuda.synchronize()
+        got[off] = [x, dz] + st
+    for a, b in zip(got[0], got[8]):
+        assert torch.equal(a, b)
+    for off in (1, 3, 6):
+        for i, (a, b) in enumerate(zip(got[0], got[off])):
+            tol = 2.0**-10 if i < 2 else 1e-6
+            assert torch.allclose(a.double(), b.double(), rtol=tol, atol=1e-6), (off, i)
+
+
 # Layers whose slices are abandoned: in 16-byte accesses, with edges, and in
 # narrower ones (the backward only).
 ABANDON_WIDE = [s for s in EXCHANGE if s.dtype in ("f16", "f32")]
