@@ -183,8 +183,7 @@ int iabn_forward_train(void *x_z, int dtype, const float *gamma, const float *be
  * blocks exchange, go to a static scratch array of 128 KiB that the library
  * holds on each device (every shape this forward runs on those kernels needs
  * at most 96 and 64 KiB; a shape that needed more would be rejected with
- * IABN_ERR_WORKSPACE).  It allocates and frees
- * nothing.  The scratch of the current device is used, so `stream` must
+ * IABN_ERR_WORKSPACE).  It allocates and frees nothing.  The scratch of the current device is used, so `stream` must
  * belong to the current device.  All calls on one device share that
  * scratch: calls that may overlap in time on one device (different streams,
  * or host threads) race and must be ordered by the caller.

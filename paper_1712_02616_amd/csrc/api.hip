@@ -527,14 +527,14 @@ const char* fwd_name(int fm) {
 // x is the input (kFwdInPlace: z on return; kFwdCkpt: xhat on return); out
 // receives z for kFwdOut and kFwdCkpt.  Everything is validated before the
 // first launch, so an error changes nothing.
-// ws_if_streaming: the workspace is checked only where the streaming
-// kernels run (the channel-resident ones use none); otherwise it must hold
-// iabn_workspace_size bytes whichever kernels run.
+// ws_if_used: the workspace is checked only where kernels that use one run
+// (the channel-resident ones and one slice per channel use none); otherwise
+// it must hold iabn_workspace_size bytes whichever kernels run.
 int forward_train_impl(int fm, void* x, void* out, int dtype, const float* gamma,
                        const float* beta, float* running_mean, float* running_var,
                        float* save_mean, float* save_var, float eps, float momentum, float slope,
                        int64_t N, int64_t C, int64_t HW, void* workspace, size_t workspace_bytes,
-                       void* stream, bool ws_if_streaming = false) {
+                       void* stream, bool ws_if_used = false) {
     int rc = validate_common(dtype, N, C, HW, true);
     if (rc) return rc;
     if (empty(N, C, HW)) return ok();
@@ -554,7 +554,7 @@ int forward_train_impl(int fm, void* x, void* out, int dtype, const float* gamma
     const Route route = plan_route(N, C, HW, dtype, g, false, fm == kFwdInPlace, &fp, &sl);
     const bool needs_ws =
         route == Route::kStream || (route == Route::kSlice && slice_workspace(sl) > 0);
-    if ((needs_ws || !ws_if_streaming) &&
+    if ((needs_ws || !ws_if_used) &&
         (rc = check_workspace(N, C, HW, workspace, workspace_bytes)))
         return rc;
     if (route == Route::kSlice) {

@@ -42,8 +42,8 @@ void launch_pointwise(int dtype, const void* src, void* dst, const TileGeom& g,
 // measured over C = 64..256 and channels of 4K..64K accesses, from C = 64
 // for the forward (C = 128, 16K accesses: 15 us against 25; 25K fp32
 // accesses: 25 against 31) and from C = 96 for the backward (C = 128, 16K
-// accesses: 27 us against 33); with larger channels, or fewer, the
-// streaming kernels are faster.
+// accesses: 27 us against 33); larger channels, or fewer, are cut into slices
+// (api.hip).
 constexpr int64_t kFusedMinChannels = 256;
 constexpr int64_t kFusedFewChannelsFwd = 64;
 constexpr int64_t kFusedFewChannelsBwd = 96;
@@ -152,8 +152,9 @@ constexpr FusedPlan kBwdLadder[] = {{256, 4}, {256, 8}, {256, 16}, {512, 16}, {1
 // 16 bytes: 14x14 or 7x7 maps in fp16, for instance) hold the same
 // elements in more, smaller registers; one ladder serves both directions.
 // Built for InPlace-ABN's own forward and backward only (the comparison
-// blocks take the streaming kernels on such shapes).  (One wave per channel
-// for the small channels of 7x7 maps measured no faster than these rungs.)
+// blocks take one slice per channel, or the streaming kernels, on such
+// shapes).  (One wave per channel for the small channels of 7x7 maps measured
+// no faster than these rungs.)
 constexpr FusedPlan kNarrowLadder[] = {{256, 4}, {256, 8}, {256, 16}, {512, 16}, {1024, 16}};
 // With at most one channel per CU, channels of 1025-2048 narrow accesses take
 // 512-thread blocks instead (2-5% faster on 14x14 and 7x7 fp16 maps with 128

@@ -4,9 +4,9 @@
 // streaming kernels read them twice and are two launches.
 //
 // Measured (backward us, before: two streaming passes, or narrow accesses):
-// (32, 64, 112x112) fp16 43.4 -> 33.6, (8, 64, 256x256) 55.2 -> 41.9 (3 b per
-// element at 4.8 TB/s), (8, 20, 224x224) bf16 21.6 -> 15.6, (8, 256, 129x129)
-// fp16 143 -> 42.3, (8, 512, 65x65) 38.0 -> 23.2, (2, 16, 8x8) fp32 4.5 -> 3.6.
+// (32, 64, 112x112) fp16 43.0 -> 32.4, (8, 64, 256x256) 54.5 -> 39.9 (3 b per
+// element at 5.0 TB/s), (8, 20, 224x224) bf16 18.4 -> 15.0, (8, 256, 129x129)
+// fp16 141 -> 41.8, (8, 512, 65x65) 35.9 -> 22.6, (2, 16, 8x8) fp32 4.9 -> 3.9.
 
 #pragma once
 

@@ -7,10 +7,12 @@
 // ragged rows; what a slice does not hold is read again.
 //
 // Measured (forward us, before: two streaming passes, or narrow accesses):
-// (32, 64, 112x112) fp16 29.3 -> 23.7, (8, 64, 256x256) 35.6 -> 27.6 (2 b per
-// element at 4.9 TB/s), (8, 20, 224x224) bf16 16.9 -> 13.3, (8, 256, 129x129)
-// fp16 115 -> 32.6, (8, 512, 65x65) 28.3 -> 16.7, (2, 16, 8x8) fp32 4.9 -> 3.9.  With the exchange left out
-// (a timing copy) the first two take 3 us less.  The code of a phase must
+// (32, 64, 112x112) fp16 27.0 -> 23.9, (8, 64, 256x256) 33.5 -> 27.3 (2 b per
+// element at 4.9 TB/s), (8, 20, 224x224) bf16 15.0 -> 13.1, (8, 256, 129x129)
+// fp16 107 -> 30.8, (8, 512, 65x65) 28.0 -> 16.3, (2, 16, 8x8) fp32 5.3 -> 4.1.
+// With the exchange left out (a timing copy) the first two take 3 us less: 2
+// for the sums to travel, the rest for filling and draining the memory system
+// around it.  The code of a phase must
 // stay short: with ragged rows' left-over elements in the unrolled loops the
 // kernel was 14000 instructions, and fetching them cost 4 us a call.
 

@@ -43,13 +43,14 @@ class Big:
 
 BIG = [
     # 4.8e9 elements per tensor: element offsets beyond 2^32 (channel 8 of
-    # sample 1 starts at 17 * 2^28); 2^29 values per channel, streaming path.
+    # sample 1 starts at 17 * 2^28); 2^29 values per channel in 56 slices.
     Big("over_2p32_elements_f16", 2, 9, 1 << 28, "f16", 41, (8,)),
     # The maximum channel count (2^20) with 16 values per channel: the
     # channel-resident path with 2-access channels, a 2^20-block grid.
     Big("max_channels_f32", 2, 1 << 20, 8, "f32", 42, (0, 1, 777, 65535, 524288, (1 << 20) - 1)),
-    # One channel of 2^28 + 3 values with an odd row length: the one-element
-    # path over a quarter billion values.
+    # One channel of 2^28 + 3 values with an odd row length: 16-byte accesses
+    # at any alignment and edges (the phases: the one-element path) over a
+    # quarter billion values.
     Big("huge_odd_channel_bf16", 1, 1, (1 << 28) + 3, "bf16", 43, (0,)),
     # 256 channels of 2^20 values: the channel-resident path with most of each
     # channel read twice (8 of every 64 strips stay in registers).
@@ -61,8 +62,11 @@ def host_f64(t: torch.Tensor) -> np.ndarray:
     return t.to(torch.float64).cpu().numpy()
 
 
-@pytest.mark.parametrize("case", BIG, ids=lambda c: c.id)
-def test_max_size_parity(case):
+# (Both large few-channel layers through the phase entry points too, which
+# run the streaming kernels.)
+@pytest.mark.parametrize("case, path", [pytest.param(c, "entry", id=c.id) for c in BIG] +
+                         [pytest.param(c, "phases", id=c.id + "_phases") for c in (BIG[0], BIG[2])])
+def test_max_size_parity(case, path):
     N, C, HW = case.N, case.C, case.HW
     say("large %s shape=%s: drawing inputs" % (case.id, (N, C, HW)))
     x, dz, prm = workloads.make_layer_device(N, C, HW, case.dtype, case.seed)
@@ -81,7 +85,11 @@ def test_max_size_parity(case):
                      dtype=torch.uint8, device="cuda")
     eps, mom, slope = 1e-5, 0.1, 0.01
     say("large %s: forward" % case.id)
-    iabn.iabn_forward_train(x, gamma, beta, rm, rv, sm, sv, eps, mom, slope, workspace=ws)
+    if path == "entry":
+        iabn.iabn_forward_train(x, gamma, beta, rm, rv, sm, sv, eps, mom, slope, workspace=ws)
+    else:
+        iabn.iabn_forward_stats(x, ws)
+        iabn.iabn_forward_apply(x, gamma, beta, rm, rv, sm, sv, eps, mom, slope, ws)
     torch.cuda.synchronize()
     g_c, b_c = prm.gamma[chans], prm.beta[chans]
     say("large %s: oracle forward on channels %s" % (case.id, chans))
@@ -96,7 +104,11 @@ def test_max_size_parity(case):
     var32 = fw["var"].astype(np.float32)
     sv[chans] = torch.from_numpy(var32).cuda()
     say("large %s: backward" % case.id)
-    iabn.iabn_backward(x, dz, gamma, beta, sv, dg, db, eps, slope, workspace=ws)
+    if path == "entry":
+        iabn.iabn_backward(x, dz, gamma, beta, sv, dg, db, eps, slope, workspace=ws)
+    else:
+        iabn.iabn_backward_reduce(x, dz, gamma, beta, slope, ws)
+        iabn.iabn_backward_apply(x, dz, gamma, beta, sv, dg, db, eps, slope, ws)
     torch.cuda.synchronize()
     say("large %s: oracle backward" % case.id)
     bw = oracle.backward_i(workloads.storage_to_f64(z_store, case.dtype), dz_s, g_c, b_c, var32,

@@ -79,8 +79,8 @@ EDGE_CASES = [
     Case("ragged_slices_bf16", 3, 4, 20008, "bf16", 18, dz_std=0.1),
     Case("ragged_odd_f32", 4, 3, 12345, "f32", 19),
     Case("many_slices_f32", 2, 2, 1 << 20, "f32", 20, dz_std=0.1),
-    # Slices of 64K fp16 values on the streaming path (fewer than 256
-    # channels): the statistics pass with its deeper batches of loads.
+    # Slices of 64K fp16 values (fewer than 256 channels): the statistics
+    # pass of the phases with its deeper batches of loads.
     Case("long_slices_f16", 8, 64, 65536, "f16", 42, dz_std=0.1),
     # Long slices with ragged ends: 8.55 accesses per thread, the last slice
     # 8.48 (one batch of 8, then a partial one), and 32.05 per thread, the

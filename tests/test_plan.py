@@ -213,15 +213,21 @@ def test_empty_and_invalid():
 
 
 def test_forward_streaming_partials_fit_the_static_scratch():
-    """The training forward takes the streaming kernels (the only ones with a
-    scratch buffer) only below 256 channels, where a call's partials never
-    exceed 96 KiB: iabn_forward_train_noalloc's 128 KiB scratch holds every
-    shape."""
+    """The training forward takes the streaming kernels only below 256
+    channels, where a call's partials never exceed 96 KiB, and the
+    slice-resident ones, which have a scratch buffer too, with at most 512
+    slices of 128 bytes that exchange sums: iabn_forward_train_noalloc's 128
+    KiB scratch holds every shape."""
     for C in (256, 300, 1024, 8192, 1 << 20):
-        for N, HW in ((1, 2), (8, 4096), (2, 1 << 20)):
+        for N, HW in ((1, 2), (8, 4096), (2, 1 << 20), (8, 4095), (2, (1 << 20) + 1)):
             if C * N * HW <= 1 << 46:
                 p = iabn.iabn_plan("forward_train", torch.float16, N, C, HW)
-                assert p["channel_resident"] == 1, (N, C, HW)
+                assert p["channel_resident"] or p["reg_accesses"], (N, C, HW)
+                assert p["blocks"] <= max(C, 512), (N, C, HW)
+    for C in range(1, 256):
+        for N, HW in ((1, 5001), (8, 65536), (2, (1 << 20) + 1)):
+            p = iabn.iabn_plan("forward_train", torch.float16, N, C, HW)
+            assert not p["reg_accesses"] or p["blocks"] <= 512, (N, C, HW)
     worst = 0
     for C in range(1, 256):
         for N, HW in ((1, 2), (2, 4096), (8, 65536), (64, 1 << 20)):

@@ -1,11 +1,11 @@
 """iabn_forward_train_noalloc, the training forward for callers that cannot
-allocate (its streaming kernels keep their partials in the library's static
-scratch), through the C ABI against iabn_forward_train with a caller's
-workspace: the same kernels, so the outputs must be bit-identical.  Two calls
-in a row on shapes that take the streaming kernels (the ones that use the
-scratch), the second smaller than the first, then a channel-resident shape
-(no scratch), then the first shape again (the scratch holds the last call's
-partials, which must not leak into the next call)."""
+allocate (the streaming kernels keep their partials, and the slice-resident
+kernels exchange their sums, in the library's static scratch), through the C
+ABI against iabn_forward_train with a caller's workspace: the same kernels, so
+the outputs must be bit-identical.  Calls in a row on shapes that use the
+scratch, one smaller than the one before, then a channel-resident shape (no
+scratch), the largest uses of either kind, and the first shape again (the
+scratch holds the last call's values, which must not leak into the next)."""
 
 from __future__ import annotations
 
@@ -22,14 +22,15 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a HIP GPU")]
 
 SHAPES = [
-    # (N, C, HW, dtype, seed): streaming (C < 64), large then smaller
-    (3, 32, 20008, "f16", 71),
-    (2, 5, 1000, "f32", 72),
-    # channel-resident (no scratch)
-    (4, 256, 1024, "bf16", 73),
-    # streaming with the most partials per call (C = 255 with big channels: 765 slices)
-    (8, 255, 65536, "f16", 74),
-    (3, 32, 20008, "f16", 71),
+    # (N, C, HW, dtype, seed, kernels): large, then smaller
+    (3, 32, 20008, "f16", 71, "streaming"),
+    (3, 5, 49, "f32", 72, "streaming"),
+    (4, 256, 1024, "bf16", 73, "channel-resident"),
+    # the most partials per call (765 slices), and nearly the most sums (510)
+    (1100, 255, 31, "f16", 75, "streaming"),
+    (8, 255, 65536, "f16", 74, "slice-resident"),
+    (3, 32, 20009, "f16", 76, "slice-resident"),
+    (3, 32, 20008, "f16", 71, "streaming"),
 ]
 
 
@@ -48,11 +49,12 @@ def run_noalloc(L: GpuLayer, eps, mom, slope):
 
 def test_noalloc_equals_workspace_forward():
     eps, mom, slope = 1e-5, 0.1, 0.01
-    for N, C, HW, dtype, seed in SHAPES:
+    for N, C, HW, dtype, seed, kernels in SHAPES:
         inp = workloads.make_layer(N, C, HW, dtype, seed, dz_std=0.1, gamma_sign=True)
         plan = iabn.iabn_plan("forward_train", TORCH_DTYPES[dtype], N, C, HW)
-        say("noalloc forward %s shape=%s channel_resident=%d" % (dtype, (N, C, HW),
-                                                                 plan["channel_resident"]))
+        say("noalloc forward %s shape=%s %s" % (dtype, (N, C, HW), kernels))
+        assert kernels == ("channel-resident" if plan["channel_resident"] else
+                           "slice-resident" if plan["reg_accesses"] else "streaming"), plan
         A = GpuLayer(inp)
         A.forward_train(eps, mom, slope)
         B = GpuLayer(inp)
