@@ -226,24 +226,26 @@ static_assert(kSliceWords * sizeof(uint64_t) <= kWaves * sizeof(Partial),
 // channels of narrow accesses stay on the streaming kernels, where the
 // training entry points give the same bits as their two phases.
 //
-// More slices are worth their exchange where a second read is slow: the
-// blocks more than fill the CUs once, and J is at least kSlicesMinJ ((32, 25,
-// 4512) fp32 J = 8 12.4 / 15.0 -> 11.2 / 12.9, (2698, 40, 48) fp16 J = 6 12.1
-// / 14.3 -> 12.3 / 15.5, but 40 blocks (300, 1, 108) fp32 J = 5 6.8 / 7.3 ->
-// 7.8 / 7.9), or kManySlicesMinJ with more than kFewSlices, whose exchange
-// takes longer ((1, 8, 512x512) fp32 J = 4 10.0 / 12.0 -> 12.2 / 12.2).  There
-// is no upper bound for 16-byte accesses ((64, 64, 224x224) fp32, J = 392: 421
-// / 697 -> 395 / 652), except where the forward reads nearly everything twice
-// and a third of the places stays empty ((8, 171, 260x260) fp16 J = 133, 342
-// blocks: 98.7 -> 107.7).  Narrower accesses are worth it in the backward only,
-// on a full chip ((3895, 20, 60) fp16 J = 10 14.5 / 17.1 -> 14.9 / 16.8, (3055,
-// 25, 52) J = 9 backward 16.4 -> 15.5, but (3233, 16, 52) J = 6 11.2 / 12.6 ->
-// 12.2 / 12.5), and up to about twice the 16 they are held deep ((64, 64,
-// 110x110) fp16 in 8-byte accesses J = 47 58.2 / 86.3 -> 77.8 / 108).
+// More slices are worth their exchange where a second read is slow: the blocks
+// more than fill the CUs once, and J is at least kSlicesMinJ ((32, 25, 4512)
+// fp32 J = 8 12.4 / 15.0 -> 11.2 / 12.9, (10, 92, 4824) bf16 J = 5 backward
+// 12.7 -> 11.7, but 8 blocks (300, 1, 108) fp32 J = 5 6.8 / 7.3 -> 7.8 / 7.9),
+// on rows shorter than a line kSlicesShortRowsMinJ ((2698, 40, 48) fp16 J = 6
+// 12.1 / 14.3 -> 12.3 / 15.5), or kManySlicesMinJ with more than kFewSlices,
+// whose exchange takes longer ((1, 8, 512x512) fp32 J = 4 10.0 / 12.0 -> 12.2 /
+// 12.2).  There is no upper bound for 16-byte accesses ((64, 64, 224x224) fp32,
+// J = 392: 421 / 697 -> 395 / 652), except where the forward reads nearly
+// everything twice and a third of the places stays empty ((8, 171, 260x260)
+// fp16 J = 133, 342 blocks: 98.7 -> 107.7).  Narrower accesses are worth it in
+// the backward only, on a full chip ((3895, 20, 60) fp16 J = 10 14.5 / 17.1 ->
+// 14.9 / 16.8, (3055, 25, 52) J = 9 backward 16.4 -> 15.5, but (3233, 16, 52) J
+// = 6 11.2 / 12.6 -> 12.2 / 12.5), and up to about twice the 16 they are held
+// deep ((64, 64, 110x110) fp16 in 8-byte accesses J = 47 58.2 / 86.3 -> 77.8 /
+// 108).
 constexpr int64_t kOneSliceMaxJ = 6;
 constexpr int64_t kOneSliceRowJ = 2;
-constexpr int64_t kSlicesMinJFwd = 7;
-constexpr int64_t kSlicesMinJBwd = 6;
+constexpr int64_t kSlicesMinJ = 5;
+constexpr int64_t kSlicesShortRowsMinJ = 7;
 constexpr int64_t kFewSlices = 32;
 constexpr int64_t kManySlicesMinJ = 16;
 constexpr int64_t kLongSliceJ = 100;
@@ -259,9 +261,10 @@ constexpr int64_t kSliceNarrowMaxJ = 32;
 // the forward of more than kFewSlices ((2, 3, 103486) fp16 Jn = 8 8.6 -> 9.9,
 // (264, 1, 1201) fp16 Jn = 32 64 blocks 10.1 -> 10.8, (164, 1, 2377) fp32 Jn =
 // 28 10.0 -> 10.9; but with more blocks than CUs (3428, 12, 99) fp16 Jn = 32
-// 15.2 -> 13.1, (4, 7, 77177) fp32 Jn = 20 12.5 -> 12.2); and with few channels
-// one short slice with more edge elements than a thread keeps ((98, 81, 95)
-// fp16 J = 5, the standard block's backward 8.9 -> 11.6).
+// 15.2 -> 13.1, (4, 7, 77177) fp32 Jn = 20 12.5 -> 12.2, (15, 12, 26572) fp16 J
+// = 5 Jn = 10 13.1 -> 11.7); and with few channels one short slice with more
+// edge elements than a thread keeps ((98, 81, 95) fp16 J = 5, the standard
+// block's backward 8.9 -> 11.6).
 constexpr int64_t kSomeSlices = 16;
 constexpr int64_t kRaggedMinNarrow = 4;
 constexpr int64_t kRaggedManyMinNarrow = 16;
@@ -282,8 +285,9 @@ bool slices_over_streaming(const SlicePlan& sl, int64_t N, int64_t C, int64_t HW
             return C >= kFusedMinChannels || J > kOneSliceMaxJ || edge_rounds_of(sl.g) <= kEdges;
         const int64_t narrow = J * 16 / ab;
         if (P > kSomeSlices && narrow <= kRaggedMinNarrow) return false;
-        return backward || P <= kFewSlices ||
-               narrow > (blocks > kCUs ? kRaggedManyMinNarrow : kRaggedManyMinNarrowFewBlocks);
+        if (backward || P <= kFewSlices) return true;
+        return blocks > kCUs ? J >= kSlicesMinJ || narrow > kRaggedManyMinNarrow
+                             : narrow > kRaggedManyMinNarrowFewBlocks;
     }
     if (ab != 16 && J > kSliceNarrowMaxJ) return false;
     if (P == 1) {
@@ -293,8 +297,8 @@ bool slices_over_streaming(const SlicePlan& sl, int64_t N, int64_t C, int64_t HW
     if (ab == 16 && P > kFewSlices) return J >= kManySlicesMinJ;
     if (blocks <= kCUs) return false;
     if (ab == 16)
-        return backward ? J >= kSlicesMinJBwd
-                        : J >= kSlicesMinJFwd && (J <= kLongSliceJ || blocks >= kLongSliceMinBlocks);
+        return J >= (HW * eb >= kLineBytes ? kSlicesMinJ : kSlicesShortRowsMinJ) &&
+               (backward || J <= kLongSliceJ || blocks >= kLongSliceMinBlocks);
     return backward && J >= kSliceNarrowMinJBwd;
 }
 

@@ -261,11 +261,12 @@ CHOICES = [
     (ALL, F32, 4, 48, 1600, "st"),
     (ALL, F16, 273, 2, 16, (2, 4)),
     (ALL, BF16, 554, 9, 8, "st"),
-    # More slices: from 7 (backward 6) accesses on a full chip, 16 where the
-    # exchange is long.
-    (ALL, F32, 32, 25, 4512, (500, 8)),
-    (("forward_train",), F16, 2698, 40, 48, "st"),
-    (("backward",), F16, 2698, 40, 48, (480, 8)),
+    # More slices: from 5 accesses on a full chip, 7 on short rows, 16 where
+    # the exchange is long.
+    (ALL, BF16, 3, 48, 29184, (480, 8)),
+    (ALL, F16, 2, 48, 29184, "st"),
+    (ALL, F16, 2698, 40, 48, "st"),
+    (ALL, F32, 3244, 48, 24, (480, 8)),
     (ALL, F32, 300, 1, 108, "st"),
     (ALL, F32, 1, 8, 512 * 512, "st"),
     (ALL, F16, 2, 8, 1024 * 1024, (512, 16)),
@@ -288,6 +289,8 @@ CHOICES = [
     (("forward_train",), F16, 264, 1, 1201, "st"),
     (("backward",), F16, 264, 1, 1201, (64, 4)),
     (("forward_train",), F32, 4, 7, 77177, (448, 8)),
+    (("forward_train",), F16, 15, 12, 26572, (504, 8)),
+    (("forward_train",), BF16, 3, 10, 48851, "st"),
     (("std_backward",), F16, 98, 81, 95, "st"),
     # Against the channel-resident kernels: one slice, several, many channels,
     # edges, short rows.
