@@ -111,7 +111,7 @@ struct SlicePlan {
     int vec;  // elements per access
     int R;    // accesses per thread the kernel holds
     int64_t J;  // accesses per thread of a slice
-    bool fine;  // backward: every element's terms to double (slice_bwd.h)
+    bool fine;  // backward, kBwdFromZ: every element's terms to double (slice_bwd.h)
 };
 
 // Rows of at least a cache line that only 2- or 4-byte accesses divide (or
@@ -349,7 +349,6 @@ bool plan_slice(int64_t N, int64_t C, int64_t HW, int eb, int vec, bool backward
     if (!best_tiles(N, C, HW, eb, v, heads, &out->g)) return false;
     out->vec = v;
     TileGeom& g = out->g;
-    out->fine = ragged;
     const Split sp = split_channel(N * HW, C);
     const int64_t groups = kThreads / g.lanes;
     auto accesses = [&](int64_t P) { return (int64_t(g.tiles) + P * groups - 1) / (P * groups); };
@@ -517,6 +516,7 @@ Route plan_route(int64_t N, int64_t C, int64_t HW, int dtype, const Geom& g, boo
     const bool channel = plan_fused(C, g, eb, backward, narrow_ok, fp);
     const Route other = channel ? Route::kChannel : Route::kStream;
     if ((channel && !ragged) || !plan_slice(N, C, HW, eb, vec, backward, sl)) return other;
+    sl->fine = channel;
     const bool slices =
         channel ? slices_over_channels(*sl, C, HW, g.vchan, eb, backward)
                 : slices_over_streaming(*sl, N, C, HW, eb, vec * eb, ragged, backward);

@@ -161,12 +161,13 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_slice_kernel(const void* __re
     sched_fence();
 
     // fp32 within one access, double across accesses (see bwd_fused_channel);
-    // on ragged rows (FINE) every element's terms go to double, as the
-    // channel-resident kernels, which move such rows an element or two at a
-    // time, add up no more in fp32: the relative error of dbeta on (8, 512,
-    // 65x65) fp16 is 2.5e-8 (8 elements in fp32: 5.0e-8).  On all rows it
-    // would cost 2-3% ((32, 64, 112x112) fp16 32.3 -> 33.2 us; there 8
-    // elements are fewer than the streaming kernels add up).
+    // where the channel-resident kernels would take the layer too, on ragged
+    // rows (FINE), every element's terms go to double, as those move such rows
+    // an element or two at a time and add up no more in fp32: the relative
+    // error of dbeta on (8, 512, 65x65) fp16 is 2.5e-8 (8 elements in fp32:
+    // 5.0e-8).  Elsewhere it would cost 2-8% ((32, 64, 112x112) fp16 32.3 ->
+    // 33.2 us, (50, 178, 1833) bf16 30.0 -> 32.3), and 8 elements are fewer than
+    // the streaming kernels add up.
     double acc_dy = 0.0, acc_dyw = 0.0;
     auto accumulate = [&](raw_t<DT, VEC> ru, raw_t<DT, VEC> rg, auto neg) {
         float tu[VEC], tg[VEC];
@@ -419,7 +420,9 @@ template <int DT, int BM>
 bool launch_dt(int vec, bool fine, const void* u, const void* zs, void* dzdx, const TileGeom& g,
                int R, const SliceArgs& sa, const BwdParams& prm, hipStream_t st) {
     constexpr int W = 16 / static_cast<int>(sizeof(typename Elem<DT>::T));
-    if (vec == W && fine) return launch_v<DT, W, BM, true>(u, zs, dzdx, g, R, sa, prm, st);
+    if constexpr (BM == kBwdFromZ) {
+        if (vec == W && fine) return launch_v<DT, W, BM, true>(u, zs, dzdx, g, R, sa, prm, st);
+    }
     if (vec == W) return launch_v<DT, W, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
     if (vec == W / 2) return launch_v<DT, W / 2, BM, false>(u, zs, dzdx, g, R, sa, prm, st);
     if constexpr (W / 4 > 1) {
